@@ -849,31 +849,21 @@ struct AttnShared {
     long long units;         // balanced mode: the unit total of all tables
     int pend_t[2];           // balanced mode: split tables of this share, and
     long long pend_u[2];     // their first units (arrivals after the walk)
+    long long own_lo, own_hi;  // own shares: this workgroup's units of the list,
+    int own_k0, own_n;       // and the table's first workgroup and share count (0: the list is cut)
 };
 
-// Exclusive prefix sum of one 64-bit value per thread of an NW-wave workgroup.
-template <int NW>
+// Exclusive prefix sum of one 64-bit value per thread (0 <= x, sum below 2^52)
+// as two 32-bit counters, its low 20 bits and the rest: block_excl_scan adds
+// those through DPP, where a 64-bit sum would pass every step through LDS.
 __device__ __forceinline__ long long wg_excl_scan(long long x, long long* lds, long long* total)
 {
-    const int l = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    long long inc = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const long long y = __shfl_up(inc, o, kWave);
-        if (l >= o) inc += y;
-    }
-    if (l == kWave - 1) lds[w] = inc;
-    __syncthreads();
-    long long before = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const long long v = lds[i];
-        before += i < w ? v : 0;
-        tot += v;
-    }
-    __syncthreads();
-    *total = tot;
-    return before + inc - x;
+    constexpr int kLow = 20;  // 1024 threads' low parts stay below 2^30
+    auto whole = [](long long p) { return ((p >> 32) << kLow) + (p & 0xffffffffLL); };
+    long long tot;
+    const long long e = block_excl_scan<long long>(((x >> kLow) << 32) | (x & ((1LL << kLow) - 1)), lds, &tot);
+    *total = whole(tot);
+    return whole(e);
 }
 
 __device__ __forceinline__ void write_empty(const AttnArgs& a, int t, int gq)
@@ -950,11 +940,50 @@ __device__ __forceinline__ bool arrive_last(const AttnArgs& a, AttnShared<GQ, NW
     return __builtin_amdgcn_readfirstlane(sh.last) != 0;
 }
 
+// The running merge {M, L, O0, O1} of one head's nsl slots, in chunks of kPre
+// whose loads are all issued before any is used: one round trip per chunk.
+template <int kPre, typename Wrote>
+__device__ __forceinline__ void merge_chunks(const float* first, long long stride, int nsl, int lane, Wrote wrote,
+                                             float& M, float& L, float& O0, float& O1)
+{
+    for (int j0 = 0; j0 < nsl; j0 += kPre) {
+        float2 ml[kPre], o[kPre];
+#pragma unroll
+        for (int j = 0; j < kPre; ++j) {  // (past the last slot: it again, unused)
+            const float* ps = first + (j0 + j < nsl ? j0 + j : nsl - 1) * stride;
+            ml[j] = get_part2(ps);
+            o[j] = get_part2(ps + 2 + 2 * lane);
+        }
+#pragma unroll
+        for (int j = 0; j < kPre; ++j) {
+            const bool ok = j0 + j < nsl && wrote(j0 + j);
+            ml[j].x = ok ? ml[j].x : -INFINITY;
+            ml[j].y = ok ? ml[j].y : 0.f;
+            o[j].x = ok ? o[j].x : 0.f;
+            o[j].y = ok ? o[j].y : 0.f;
+        }
+        float Mn = M;
+#pragma unroll
+        for (int j = 0; j < kPre; ++j) Mn = fmax_sel(Mn, ml[j].x);
+        if (Mn == -INFINITY) continue;  // only empty states so far
+        const float f0 = __builtin_amdgcn_exp2f(M - Mn);  // 0 before the first state
+        M = Mn;
+        L *= f0;
+        O0 *= f0;
+        O1 *= f0;
+#pragma unroll
+        for (int j = 0; j < kPre; ++j) {
+            const float f = __builtin_amdgcn_exp2f(ml[j].x - M);  // 0 for slots without a state
+            L = fmaf(ml[j].y, f, L);
+            O0 = fmaf(o[j].x, f, O0);
+            O1 = fmaf(o[j].y, f, O1);
+        }
+    }
+}
+
 // Output of table t from the partial states of its nsl share slots at `base`
 // (slot j at base + j * GQ * kPartStride; wrote(j): slot j holds a state), in
-// page order.  One wave per query head, lane = dims 2*lane, 2*lane+1; the
-// first kPre slots' loads are all issued before any is used (one round trip
-// for the usual two to five shares of a table).
+// page order.  One wave per query head, lane = dims 2*lane, 2*lane+1.
 template <int GQ, typename Wrote>
 __device__ __forceinline__ void merge_parts(const AttnArgs& a, int t, const float* base, int nsl, Wrote wrote)
 {
@@ -964,38 +993,12 @@ __device__ __forceinline__ void merge_parts(const AttnArgs& a, int t, const floa
     const long long stride = (long long)GQ * kPartStride;
     static_assert(GQ <= 8, "one wave per query head (eight or more waves)");
     if (hh < GQ) {
-        const float* pr = base + hh * kPartStride;
-        constexpr int kPre = 8;
-        float2 ml[kPre], o[kPre];
-#pragma unroll
-        for (int j = 0; j < kPre; ++j) {
-            const bool ok = j < nsl && wrote(j);
-            ml[j] = ok ? get_part2(pr + j * stride) : make_float2(-INFINITY, 0.f);
-            o[j] = ok ? get_part2(pr + j * stride + 2 + 2 * lane) : make_float2(0.f, 0.f);
-        }
-        float M = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < kPre; ++j) M = fmax_sel(M, ml[j].x);
-        for (int j = kPre; j < nsl; ++j)
-            if (wrote(j)) M = fmax_sel(M, get_part2(pr + j * stride).x);
-        float L = 0.f, O0 = 0.f, O1 = 0.f;
-        if (M != -INFINITY) {
-#pragma unroll
-            for (int j = 0; j < kPre; ++j) {
-                const float f = __builtin_amdgcn_exp2f(ml[j].x - M);  // 0 for slots without a state
-                L = fmaf(ml[j].y, f, L);
-                O0 = fmaf(o[j].x, f, O0);
-                O1 = fmaf(o[j].y, f, O1);
-            }
-            for (int j = kPre; j < nsl; ++j) {
-                if (!wrote(j)) continue;
-                const float2 mj = get_part2(pr + j * stride), oj = get_part2(pr + j * stride + 2 + 2 * lane);
-                const float f = __builtin_amdgcn_exp2f(mj.x - M);
-                L = fmaf(mj.y, f, L);
-                O0 = fmaf(oj.x, f, O0);
-                O1 = fmaf(oj.y, f, O1);
-            }
-        }
+        float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f;
+        const float* first = base + hh * kPartStride;
+        if (nsl <= 4)
+            merge_chunks<4>(first, stride, nsl, lane, wrote, M, L, O0, O1);
+        else
+            merge_chunks<8>(first, stride, nsl, lane, wrote, M, L, O0, O1);
         const long long row = (long long)b * a.Hq + h * GQ + hh;
         *reinterpret_cast<float2*>(a.out + row * kD + 2 * lane) =
             (L > 0.f) ? make_float2(O0 / L, O1 / L) : make_float2(0.f, 0.f);
@@ -1265,7 +1268,8 @@ __device__ __forceinline__ void run_segment(const AttnArgs& a, AttnShared<GQ, NW
 // attn_decode.
 //  splits = S >= 1: workgroup t*S + c takes range c of table t's pages, cut
 //    into min(S, pages) equal ranges (S = 1: no split).
-//  splits = 0: balanced shares.  All tables' pages, in table order, form one
+//  splits = -1: balanced shares.  Where own_shares() says so, each table is cut
+//    into ranges of its own.  Otherwise all tables' pages, in table order, form one
 //    list of U work units; workgroup k of W owns the pages whose first unit
 //    lies in [k*U/W, (k+1)*U/W).  Each workgroup finds its first table with a
 //    prefix sum over the tables' units, then walks its tables.  A table lying
@@ -1410,6 +1414,35 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
     return tab[0];
 }
 
+// Balanced mode with little work per workgroup: each table gets shares of its own.
+// A call of eight 600-token tables has 136 pages for 512 workgroups; one equal cut
+// of the concatenated list gives a table 64 shares of a page or none, whose
+// arrivals and merge were the whole call (190 us; 10.5 now).  Shares that cross a
+// table boundary also cost a second segment start and a second arrival.  So every
+// table is cut into ceil(p / quantum) equal ranges of its p page units, one
+// workgroup each, a table in one range having no merge, with quantum the largest of
+//   total / (W - T)     the ranges of T tables then fit the W workgroups;
+//   kOwnMin             a high page for every wave of the workgroup;
+//   kOwnRoot * sqrt(p)  a share's walk takes time in proportion to the quantum, the
+//                       merge in proportion to p / quantum, so the best quantum
+//                       grows with sqrt(p): 24, 49 and 112 units measured best on
+//                       tables of 244, 780 and 3122 (11.7, 13.4 and 19.0 us for one
+//                       sequence of 2500, 8000 and 32768 tokens at GQ 4; 144, 129
+//                       and 105 before).
+// Rounding up to whole ranges makes the longest share total / (W - T) where the cut
+// list has total / W plus a segment's start, so the line lies where the two
+// differ by Units::seg (16 sequences of 2000 tokens, 128 tables: 16.5 against
+// 19.8 us; of 8192 tokens, over the line: 37 us cut).
+template <int LI, int NW>
+constexpr int kOwnMin = NW * Units<LI>::hi;
+constexpr float kOwnRoot = 2.0f;
+
+template <int LI>
+__device__ __forceinline__ bool own_shares(long long total, int T, long long W)
+{
+    return T < W && total * T <= Units<LI>::seg * W * (W - T);
+}
+
 template <int GQ, int LI>
 __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, LI)) void attn_decode(AttnArgs a)
 {
@@ -1451,7 +1484,12 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
     long long units[kKeep];
     long long mine = 0;
     {
-        // all loads first (clamped to a valid table), then the units
+        // all loads first (clamped to a valid table), then the units; thread 0
+        // also claims the arrival word of table blockIdx.x for this call (the
+        // shares of a split table arrive together: without the claim each
+        // retries a compare-and-swap against the others, 2 us per share)
+        const bool claim = threadIdx.x == 0 && k < T;
+        const unsigned long long word = claim ? arrive_peek(a.arrive + k) : 0ull;
         int lh[kKeep], ll[kKeep];
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) {
@@ -1466,6 +1504,7 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
             // an empty table's output comes from workgroup t % W
             if (t0 + i < t1 && units[i] == 0 && (t0 + i) % W == k) write_empty_one(a, t0 + i, GQ);
         }
+        if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
     }
     for (int t = t0 + kKeep; t < t1; ++t) {
         const long long u = table_info<LI>(a, t).units;
@@ -1473,24 +1512,67 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
         if (u == 0 && t % W == k) write_empty_one(a, t, GQ);
     }
     long long total;
-    const long long before = wg_excl_scan<NW>(mine, sh.scan, &total);
-    if (threadIdx.x == 0) sh.units = total;  // read back by the arrival (not kept in registers)
-    const long long b_lo = k * total / W, b_hi = (k + 1) * total / W;
-    if (b_lo >= b_hi) return;
-    long long u = before;
-    for (int t = t0; t < t1; ++t) {  // exactly one table holds unit b_lo
-        const int i = t - t0;
-        long long n = 0;
-#pragma unroll
-        for (int j = 0; j < kKeep; ++j) n = i == j ? units[j] : n;
-        if (i >= kKeep) n = table_info<LI>(a, t).units;
-        if (u <= b_lo && b_lo < u + n) {
-            sh.t_first = t;
-            sh.u_first = u;
-        }
-        u += n;
+    const long long before = wg_excl_scan(mine, sh.scan, &total);
+    if (threadIdx.x == 0) {
+        sh.units = total;  // read back by the arrival (not kept in registers)
+        sh.own_n = 0;
     }
-    __syncthreads();
+    long long b_lo, b_hi;
+    if (own_shares<LI>(total, T, W)) {
+        const int room = (int)(W - T);
+        const int need = (int)((total + room - 1) / room);
+        const int least = need > kOwnMin<LI, NW> ? need : kOwnMin<LI, NW>;
+        auto shares_of = [&](long long un) {
+            if (un <= 0) return 0;
+            const int pu = (int)un - Units<LI>::seg;
+            const int root = (int)(kOwnRoot * __builtin_sqrtf((float)pu));
+            const int quantum = root > least ? root : least;
+            return (pu + quantum - 1) / quantum;
+        };
+        int cnt = 0;
+        for (int t = t0; t < t1; ++t) cnt += shares_of(t == t0 ? units[0] : table_info<LI>(a, t).units);
+        int all;
+        int at = block_excl_scan<int>(cnt, reinterpret_cast<int*>(sh.scan), &all);
+        if (k >= all) return;
+        long long u = before;
+        for (int t = t0; t < t1; ++t) {
+            const long long un = t == t0 ? units[0] : table_info<LI>(a, t).units;
+            const int n = shares_of(un);
+            if (at <= k && k < at + n) {
+                const int c = (int)k - at, pu = (int)un - Units<LI>::seg;
+                sh.t_first = t;
+                sh.u_first = u;
+                sh.own_k0 = at;
+                sh.own_n = n;
+                // share c: page units [c*pu/n, (c+1)*pu/n), the first also the table's start
+                sh.own_lo = u + (c == 0 ? 0 : Units<LI>::seg + (long long)c * pu / n);
+                sh.own_hi = u + Units<LI>::seg + (long long)(c + 1) * pu / n;
+            }
+            at += n;
+            u += un;
+        }
+        __syncthreads();
+        b_lo = read_lane<long long>(sh.own_lo, 0);
+        b_hi = read_lane<long long>(sh.own_hi, 0);
+    } else {
+        b_lo = k * total / W;
+        b_hi = (k + 1) * total / W;
+        if (b_lo >= b_hi) return;
+        long long u = before;
+        for (int t = t0; t < t1; ++t) {  // exactly one table holds unit b_lo
+            const int i = t - t0;
+            long long n = 0;
+#pragma unroll
+            for (int j = 0; j < kKeep; ++j) n = i == j ? units[j] : n;
+            if (i >= kKeep) n = table_info<LI>(a, t).units;
+            if (u <= b_lo && b_lo < u + n) {
+                sh.t_first = t;
+                sh.u_first = u;
+            }
+            u += n;
+        }
+        __syncthreads();
+    }
     int t = __builtin_amdgcn_readfirstlane(sh.t_first);
     long long ut = read_lane<long long>(sh.u_first, 0);
     // A share holds at most two split tables, its first and its last (the
@@ -1524,6 +1606,13 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
         __syncthreads();
         const int tp = __builtin_amdgcn_readfirstlane(sh.pend_t[i]);
         const long long up = read_lane<long long>(sh.pend_u[i], 0);
+        const int own_n = __builtin_amdgcn_readfirstlane(sh.own_n);
+        if (own_n > 0) {
+            const int k0 = __builtin_amdgcn_readfirstlane(sh.own_k0);
+            if (arrive_last<GQ>(al, sh, tp, own_n))
+                merge_parts<GQ>(al, tp, al.part + ((long long)k0 + tp) * GQ * kPartStride, own_n, [](int) { return true; });
+            continue;
+        }
         const long long U = read_lane<long long>(sh.units, 0);
         const long long units = table_info<LI>(al, tp).units;
         // shares kf .. kl own the table's units (the owner of unit x is the

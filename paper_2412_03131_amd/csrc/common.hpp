@@ -253,6 +253,20 @@ __device__ __forceinline__ void arrive_claim(unsigned long long* w, unsigned lon
     }
 }
 
+// The same in one attempt whose outcome is not waited for, on a word read before
+// (arrive_peek): the exchange fails only where the word changed since, i.e.
+// where an arrival of this call has taken it over already.
+__device__ __forceinline__ unsigned long long arrive_peek(unsigned long long* w)
+{
+    return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void arrive_claim_once(unsigned long long* w, unsigned long long old, unsigned long long tag)
+{
+    if ((old >> kArriveCountBits) != tag)
+        (void)__hip_atomic_compare_exchange_strong(w, &old, tag << kArriveCountBits, __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Block-wide sum of a true 64-bit value and OR of flag bits (all threads get
 // the result).  `lds` must hold blockDim.x/64 + 1 entries.
 __device__ __forceinline__ long long block_sum_or(long long x, uint32_t bits, long long* lds,
