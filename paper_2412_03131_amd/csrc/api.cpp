@@ -348,11 +348,11 @@ diffkv_status diffkv_quantize_append(const diffkv_layout* layout, const diffkv_c
     a.tplan = reinterpret_cast<long long*>(base + w.tplan);
     a.job_table = reinterpret_cast<int32_t*>(base + w.job_table);
     a.job_cap = (int)w.max_jobs;
-    // without a planning launch every commit workgroup reads all tables' plan
-    // state once, so the grid is capped lower; workgroups loop over the jobs
-    // beyond it
+    // workgroups of four page jobs; without a planning launch every one of them reads all
+    // tables' plan state once, so the grid is capped lower; they loop over the jobs beyond it
     const int64_t cap = append_planned(B, H) ? 4096 : 1024;
-    int64_t grid = w.max_jobs < cap ? w.max_jobs : cap;
+    const int64_t groups = (w.max_jobs + kAppendJobsPerGroup - 1) / kAppendJobsPerGroup;
+    int64_t grid = groups < cap ? groups : cap;
     if (grid < 1) grid = 1;
     hipError_t e = launch_append(a, (int)grid, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? DIFFKV_OK : DIFFKV_E_LAUNCH;

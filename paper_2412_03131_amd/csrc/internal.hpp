@@ -55,6 +55,7 @@ struct AppendArgs : LayoutArgs {
 // Above this many tables an append plans once in its own launch instead of in
 // every commit workgroup.
 constexpr int kAppendPlanTables = 1024;
+constexpr int kAppendJobsPerGroup = 4;  // page jobs a commit workgroup runs side by side (one per wave)
 inline bool append_planned(long long B, long long Hkv) { return B * Hkv > kAppendPlanTables; }
 
 struct AllocArgs {

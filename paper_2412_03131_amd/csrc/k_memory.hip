@@ -10,9 +10,9 @@
 //                    results (page demand per table, one prefix sum over
 //                    tables, all-or-nothing check against the free region and
 //                    the table width); workgroup 0 writes the new state, and
-//                    all take (table, section, page) jobs: resolve the page ID
-//                    (new pages from the table's ring region), quantize each
-//                    token's 32-dim groups and write the page.
+//                    every wave takes (table, section, page) jobs: resolve the
+//                    page ID (new pages from the table's ring region), quantize
+//                    each token's 32-dim groups, write the page.
 //   append_one       a call of at most one new token per sequence (a decode
 //                    step) in one launch: classes, plan and page jobs, the
 //                    state written by the last workgroup to finish.
@@ -315,11 +315,9 @@ constexpr int kPlanThreads = 1024;
 // pages, seq_len, ring head) while all of them -- reading only the snapshot
 // -- take page jobs (table, section, page) in job order.
 // ---------------------------------------------------------------------------
-constexpr int kQuantWaves = 4;
+constexpr int kQuantWaves = kAppendJobsPerGroup;  // page jobs a workgroup runs side by side, one per wave
 constexpr int kCommitThreads = kQuantWaves * kWave;
-constexpr int kTokIlp = 4;    // tokens a wave quantizes side by side
-constexpr int kTokLoad = 8;   // tokens a wave loads up front: a 32-token page in one round of loads
-static_assert(kTokLoad * kQuantWaves >= 32, "one round of loads per page");
+constexpr int kCommitWaves = 4;  // waves per SIMD of the bulk commit: 3 measured 194, 4 169, 5 (spills) 183 us
 
 struct TablePlan {
     int need[2], jobs[2];
@@ -385,188 +383,222 @@ __device__ __forceinline__ void describe_job(JobDesc& d, int t, const TState& s,
     d.sold = 0;
 }
 
-// One page job: resolve the page ID (a new page from the table's ring region),
-// quantize the job's tokens and write them, zero a fresh page's unused bytes.
-// Called by every thread of the workgroup after `s_job` is described.
-// V code rows: a lane owns dims 2*lane, 2*lane+1, i.e. 2 * T * vb / 8 bytes (8,
-// 16 or 32) of the V code segment, kept as up to eight 32-bit words.
-constexpr int kRowWords = 8;
+// The image of one page, as the job's wave composes it in LDS.
+constexpr int kPageMax = 4736;  // largest page of the layouts
+constexpr bool page_max_covers(int li) { return li >= kNumLayouts || (layout_page_bytes(li) <= kPageMax && page_max_covers(li + 1)); }
+static_assert(page_max_covers(0), "page image");
+struct PageImage {
+    uint4 b[kPageMax / 16];
+};
 
+// One page job, by one wave: resolve the page ID (a new page from the table's
+// ring region), quantize the job's tokens, write them, zero a fresh page's
+// unused bytes.  Lane = (row of 16, eight dims): row r takes the TT/4 page
+// slots from r * TT/4 on, one per step, so a token's key or value vector is one
+// 16-byte load per lane, a quad holds a 32-dim group, and a lane ends with its
+// dims' codes of TT/4 neighbouring slots, one piece of each dimension-major
+// value row.  The page is composed in LDS and written in 16-byte pieces: a fresh
+// page whole, a continued one by its new slots (its value rows or-ed with the
+// old).
+// Bound by HBM on bulk appends (fp16 rows in, pages out): 132 us for 64 prompts
+// of 1k-4k tokens at 8 KV heads (1.3M token-heads, 60 % kept, 0.55 GB: 4.2 TB/s
+// where a large copy reaches 5.1).  One wave per token with two values per
+// lane, its codes stored where they fell, took 576 us: about 250 instructions
+// per token, most of them for the sixteenfold group extremes and scale.
 template <int KB, int VB, int TT>
-__device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDesc& s_job,
-                                               uint32_t (*s_rows)[kWave][kRowWords])
+__device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDesc& job, PageImage& img_)
 {
-    const int tid = threadIdx.x;
-    const int P = a.p_max;
+    constexpr int kLbK = (1 << KB) - 1, kLbV = (1 << VB) - 1;
+    constexpr int NS = TT / 4;                  // slots per row of lanes
+    constexpr int kStep = 2;                    // slots per row loaded at once (four: 128 VGPRs and spills)
+    constexpr int kAcc = NS * VB > 24 ? 2 : 1;  // value codes of NS slots: exact in one or two floats
+    constexpr int kPer = NS / kAcc;
+    constexpr int kVBytes = kD * TT * VB / 8;
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = wave_index();
-    const int grp = lane >> 4;
-    const int H = a.Hkv;
-    const long long page_bytes = a.page_bytes;
-    const int t = __builtin_amdgcn_readfirstlane(s_job.t);
-    const int sec = __builtin_amdgcn_readfirstlane(s_job.sec);
-    const int p = __builtin_amdgcn_readfirstlane(s_job.p);
-    const int u0 = __builtin_amdgcn_readfirstlane(s_job.u0);
-    const int u1 = __builtin_amdgcn_readfirstlane(s_job.u1);
-    const int lold = __builtin_amdgcn_readfirstlane(s_job.lold);
-    const int n = __builtin_amdgcn_readfirstlane(s_job.n);
-    const int tslot = __builtin_amdgcn_readfirstlane(s_job.tslot);
-    const long long ring_idx = s_job.ring_idx;
-    const int b = t / H, h = t - b * H;
-    constexpr int kb = KB, vb = VB;
-    constexpr int rw = TT * VB / 32;  // 32-bit words per dimension row (1, 2 or 4)
-    static_assert(2 * rw <= kRowWords, "value rows");
-    // the page ID (every wave reads the one entry), beside the token loads
+    const int row = lane >> 4, l16 = lane & 15;
+    const int P = a.p_max, H = a.Hkv, sec = job.sec;
+    const int t = job.t, b = t / H, h = t - b * H;
+    uint8_t* img = reinterpret_cast<uint8_t*>(&img_);
+    // the page ID, beside the token loads
     int32_t* trow = a.page_table + (long long)t * P;
-    int id = ring_idx < 0 ? trow[tslot] : a.ring[ring_idx % a.num_pages];
+    int id = job.ring_idx < 0 ? trow[job.tslot] : a.ring[job.ring_idx % a.num_pages];
+    const int off_b = job.one ? job.off_b : a.row_off[b];
+    const int sold = job.one ? job.sold : a.sold[b];
+    // slots [s0, s1) are the job's; lane s < TT: the token of slot s, row
+    // ord[u - lold] of its sequence (high, rank order) or ord[n - 1 - (u - lold)]
+    // (low ranks are stored from the back); other lanes repeat slot s0's
+    const int s0 = job.u0 - job.p * TT, s1 = job.u1 - job.p * TT;
+    const bool mine = lane >= s0 && lane < s1;
+    int j = 0;
+    if (!job.one) {
+        const int32_t* ord = a.ord + (long long)off_b * H + (long long)h * job.n;
+        const int r = job.p * TT + (mine ? lane : s0) - job.lold;
+        j = ord[sec ? job.n - 1 - r : r];
+    }
+    const float score = a.score[(long long)(off_b + j) * H + h];
+    // (uniform) some row's slot of step i is the job's
+    auto step_on = [&](int i) { return s1 - s0 >= NS || ((i - s0) & (NS - 1)) < s1 - s0; };
+    uint4 kx[kStep], vx[kStep];
+    auto load_steps = [&](int i0) {
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+            kx[i] = vx[i] = make_uint4(0, 0, 0, 0);
+            if (step_on(i0 + i)) {
+                const int jt = __shfl(j, NS * row + i0 + i, kWave);
+                const long long at = ((long long)(off_b + jt) * H + h) * (kD / 8) + l16;
+                kx[i] = reinterpret_cast<const uint4*>(a.k)[at];
+                vx[i] = reinterpret_cast<const uint4*>(a.v)[at];
+            }
+        }
+    };
+    load_steps(0);
     id = __builtin_amdgcn_readfirstlane(id);
-    if (tid == 0 && ring_idx >= 0) trow[tslot] = id;
-    // this wave's tokens u0 + wave + kQuantWaves*i, all loaded up front; token
-    // u of the section is row ord[u - lold] (high, rank order) or
-    // ord[n - 1 - (u - lold)] (low ranks are stored from the back)
-    const bool one = __builtin_amdgcn_readfirstlane(s_job.one) != 0;  // the job's one token is row 0 of its sequence
-    const int off_b = one ? __builtin_amdgcn_readfirstlane(s_job.off_b) : a.row_off[b];
-    const int sold = one ? __builtin_amdgcn_readfirstlane(s_job.sold) : a.sold[b];
-    const int32_t* ord = a.ord + (long long)off_b * H + (long long)h * n;
-    int jj[kTokLoad];
-    uint32_t kx[kTokLoad], vx[kTokLoad];
-#pragma unroll
-    for (int i = 0; i < kTokLoad; ++i) {
-        const int u = u0 + wave + i * kQuantWaves;
-        const int r = (u < u1 ? u : u0) - lold;
-        jj[i] = one ? 0 : (sec ? ord[n - 1 - r] : ord[r]);
-    }
-#pragma unroll
-    for (int i = 0; i < kTokLoad; ++i) {
-        const long long row = (long long)(off_b + jj[i]) * H + h;
-        kx[i] = reinterpret_cast<const uint32_t*>(a.k + row * kD)[lane];
-        vx[i] = reinterpret_cast<const uint32_t*>(a.v + row * kD)[lane];
-    }
+    if (lane == 0 && job.ring_idx >= 0) trow[job.tslot] = id;
     const int off_kc = a.off_kcode[sec], off_km = a.off_kmeta[sec];
     const int off_vc = a.off_vcode[sec], off_vm = a.off_vmeta[sec];
-    const bool fresh = (u0 == p * TT);
+    const int off_sc = a.off_score[sec], off_pos = a.off_pos[sec];
+    const bool fresh = s0 == 0;
     const bool page_ok = (unsigned)id < (unsigned)a.num_pages;  // never write outside the pool
-    uint8_t* pg = a.pool + (long long)(page_ok ? id : 0) * page_bytes;
-    // a page being continued keeps its earlier tokens' V code bits
-    uint32_t vold[kRowWords] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (wave == 0 && page_ok && !fresh) {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(pg + off_vc) + lane * 2 * rw;
+    uint8_t* pg = a.pool + (long long)(page_ok ? id : 0) * a.page_bytes;
+    // a page being continued keeps its earlier tokens' value code bits
+    uint4 vold[(kVBytes + 1023) / 1024];
 #pragma unroll
-        for (int w = 0; w < kRowWords; ++w)
-            if (w < 2 * rw) vold[w] = src[w];
-    }
-    if (page_ok && fresh) {
-        // A fresh page reads as zero wherever no token lies: zero the token
-        // slots from u1 on in every per-token segment and the page tail.
-        // These bytes are disjoint from the ones the tokens write (V code
-        // rows are written whole, zeros included), so the stores need no
-        // ordering among themselves.
-        const int s_end = u1 - p * TT, nfill = TT - s_end;
-        const uint4 z4 = make_uint4(0, 0, 0, 0);
-        for (int i = tid; i < (kb + 1) * nfill; i += kCommitThreads) {
-            const int c = i / nfill, sl = s_end + (i - c * nfill);  // K chunks (kb per token), then K meta
-            uint8_t* dst = c < kb ? pg + off_kc + (c * TT + sl) * 16 : pg + off_km + sl * 16;
-            *reinterpret_cast<uint4*>(dst) = z4;
-        }
-        for (int i = tid; i < (kNG + 2) * nfill; i += kCommitThreads) {
-            const int g = i / nfill, sl = s_end + (i - g * nfill);  // V meta groups, score, pos
-            uint8_t* dst = g < kNG ? pg + off_vm + (g * TT + sl) * 4
-                                   : pg + (g == kNG ? a.off_score[sec] : a.off_pos[sec]) + sl * 4;
-            *reinterpret_cast<uint32_t*>(dst) = 0;
-        }
-        for (long long o = a.off_pos[sec] + (long long)TT * 4 + tid * 16; o < page_bytes; o += kCommitThreads * 16)
-            *reinterpret_cast<uint4*>(pg + o) = z4;
-    }
-    uint32_t rows[kRowWords] = {0, 0, 0, 0, 0, 0, 0, 0};  // dim 2*lane: words 0 .. rw-1, dim 2*lane+1: rw ..
-    // two passes of kTokIlp tokens: quantize side by side, then store
+    for (int i = 0; i < (kVBytes + 1023) / 1024; ++i)
+        vold[i] = !fresh && 1024 * i + 16 * lane < kVBytes ? *reinterpret_cast<const uint4*>(pg + off_vc + 1024 * i + 16 * lane)
+                                                           : make_uint4(0, 0, 0, 0);
+    if (fresh)  // zero what no token covers: of a full page, the bytes past its segments
+        for (int o = (s1 < TT ? 0 : off_pos / 16 + TT / 4) + lane; o < (int)a.page_bytes / 16; o += kWave)
+            img_.b[o] = make_uint4(0, 0, 0, 0);
+    wave_lds_sync();
+    float vrow[kAcc][8];
 #pragma unroll
-    for (int pass = 0; pass < kTokLoad / kTokIlp; ++pass) {
-        const int base_u = u0 + wave + pass * kTokIlp * kQuantWaves;
-        if (base_u >= u1) break;  // wave-uniform: no token of this wave left in the page
-        uint32_t ksz[kTokIlp], kc0[kTokIlp], kc1[kTokIlp], vsz[kTokIlp], vc0[kTokIlp], vc1[kTokIlp];
+    for (int q = 0; q < kAcc; ++q)
 #pragma unroll
-        for (int i = 0; i < kTokIlp; ++i) {
-            if (base_u + i * kQuantWaves < u1) {
-                quant_pair(kx[pass * kTokIlp + i], (1 << kb) - 1, ksz[i], kc0[i], kc1[i]);
-                quant_pair(vx[pass * kTokIlp + i], (1 << vb) - 1, vsz[i], vc0[i], vc1[i]);
-            }
-        }
+        for (int d = 0; d < 8; ++d) vrow[q][d] = 0.0f;
+#pragma unroll 1
+    for (int i0 = 0; i0 < NS; i0 += kStep) {
+        if (i0 > 0) load_steps(i0);
 #pragma unroll
-        for (int i = 0; i < kTokIlp; ++i) {
-            const int u = base_u + i * kQuantWaves;
-            if (u >= u1) break;
-            const int sl = u - p * TT;
-            const int bit = sl * vb;
-#pragma unroll
-            for (int w = 0; w < kRowWords / 2; ++w) {
-                if (w == (bit >> 5) && w < rw) {
-                    rows[w] |= vc0[i] << (bit & 31);
-                    rows[rw + w] |= vc1[i] << (bit & 31);
+        for (int i = 0; i < kStep; ++i) {
+            if (!step_on(i0 + i)) continue;
+            const int sl = NS * row + i0 + i;
+            const bool on = sl >= s0 && sl < s1;
+            uint32_t ksz, vsz;
+            float c[8];
+            quant_oct<kLbK>(kx[i], ksz, c);
+            if (on) {
+                auto f = [](float x, float m, float y) { return __builtin_fmaf(x, m, y); };
+                if constexpr (KB == 8) {  // bytes 8 * (l16 & 1) .. of chunk l16 / 2
+                    uint2 w;
+                    w.x = (uint32_t)f(c[1], 256.0f, c[0]) | (uint32_t)f(c[3], 256.0f, c[2]) << 16;
+                    w.y = (uint32_t)f(c[5], 256.0f, c[4]) | (uint32_t)f(c[7], 256.0f, c[6]) << 16;
+                    *reinterpret_cast<uint2*>(img + off_kc + ((l16 >> 1) * TT + sl) * 16 + 8 * (l16 & 1)) = w;
+                } else {  // bytes 4 * (l16 & 3) .. of chunk l16 / 4
+                    const uint32_t w = (uint32_t)f(f(f(c[3], 16.0f, c[2]), 16.0f, c[1]), 16.0f, c[0]) |
+                                       (uint32_t)f(f(f(c[7], 16.0f, c[6]), 16.0f, c[5]), 16.0f, c[4]) << 16;
+                    *reinterpret_cast<uint32_t*>(img + off_kc + ((l16 >> 2) * TT + sl) * 16 + 4 * (l16 & 3)) = w;
                 }
             }
-            if (!page_ok) continue;
-            const long long row = (long long)(off_b + jj[pass * kTokIlp + i]) * H + h;
-            if (kb == 8) {
-                uint16_t* dst = reinterpret_cast<uint16_t*>(pg + off_kc + ((lane >> 3) * TT + sl) * 16 +
-                                                            ((2 * lane) & 15));
-                *dst = (uint16_t)(kc0[i] | (kc1[i] << 8));
-            } else {
-                uint8_t* dst = pg + off_kc + (grp * TT + sl) * 16 + (lane & 15);
-                *dst = (uint8_t)(kc0[i] | (kc1[i] << 4));
+            quant_oct<kLbV>(vx[i], vsz, c);
+            const float place = on ? (float)(1 << VB * ((i0 + i) % kPer)) : 0.0f;
+#pragma unroll
+            for (int q = 0; q < kAcc; ++q) {
+                const float at = (i0 + i) / kPer == q ? place : 0.0f;
+#pragma unroll
+                for (int d = 0; d < 8; ++d) vrow[q][d] = __builtin_fmaf(c[d], at, vrow[q][d]);
             }
-            if ((lane & 15) == 0) {
-                *reinterpret_cast<uint32_t*>(pg + off_km + (sl * kNG + grp) * 4) = ksz[i];
-                *reinterpret_cast<uint32_t*>(pg + off_vm + (grp * TT + sl) * 4) = vsz[i];
-            }
-            if (lane == 0) {
-                reinterpret_cast<float*>(pg + a.off_score[sec])[sl] = a.score[row];
-                reinterpret_cast<int32_t*>(pg + a.off_pos[sec])[sl] = sold + jj[pass * kTokIlp + i];
+            if (on && (l16 & 3) == 0) {
+                *reinterpret_cast<uint32_t*>(img + off_km + (sl * kNG + (l16 >> 2)) * 4) = ksz;
+                *reinterpret_cast<uint32_t*>(img + off_vm + ((l16 >> 2) * TT + sl) * 4) = vsz;
             }
         }
     }
-    // the page's dimension-major V code rows: OR of the waves' bits (and of the
-    // bits already on a page being continued), one store per dimension pair
+    // value rows: the piece of slots NS*row .. of dims 8*l16 ..
 #pragma unroll
-    for (int w = 0; w < kRowWords; ++w) s_rows[wave][lane][w] = rows[w];
-    __syncthreads();
-    if (wave == 0 && page_ok) {
-        uint32_t* dst = reinterpret_cast<uint32_t*>(pg + off_vc) + lane * 2 * rw;
-#pragma unroll
-        for (int w = 0; w < kRowWords; ++w) {
-            uint32_t x = vold[w];
-#pragma unroll
-            for (int q = 0; q < kQuantWaves; ++q) x |= s_rows[q][lane][w];
-            if (w < 2 * rw) dst[w] = x;
+    for (int d = 0; d < 8; ++d) {
+        uint8_t* at = img + off_vc + (8 * l16 + d) * (TT * VB / 8) + row * (NS * VB / 8);
+        if constexpr (NS * VB == 32) {
+            *reinterpret_cast<uint32_t*>(at) = (uint32_t)vrow[0][d] | (uint32_t)vrow[kAcc - 1][d] << 16;
+        } else if constexpr (NS * VB == 16) {
+            *reinterpret_cast<uint16_t*>(at) = (uint16_t)(uint32_t)vrow[0][d];
+        } else {
+            static_assert(NS * VB == 8, "value row pieces");
+            *at = (uint8_t)(uint32_t)vrow[0][d];
         }
     }
+    if (mine) {
+        *reinterpret_cast<float*>(img + off_sc + 4 * lane) = score;
+        *reinterpret_cast<int32_t*>(img + off_pos + 4 * lane) = sold + j;
+    }
+    wave_lds_sync();
+    if (page_ok && fresh) {
+        for (int o = lane; o < (int)a.page_bytes / 16; o += kWave) reinterpret_cast<uint4*>(pg)[o] = img_.b[o];
+    } else if (page_ok) {
+        const int ns = s1 - s0;
+        for (int i = lane; i < (KB + 1) * ns; i += kWave) {  // key chunks, then key metadata
+            const int c = i / ns, sl = s0 + (i - c * ns);
+            const int o = c < KB ? off_kc + (c * TT + sl) * 16 : off_km + sl * 16;
+            *reinterpret_cast<uint4*>(pg + o) = *reinterpret_cast<const uint4*>(img + o);
+        }
+        for (int i = lane; i < (kNG + 2) * ns; i += kWave) {  // value metadata, score, position
+            const int g = i / ns, sl = s0 + (i - g * ns);
+            const int o = g < kNG ? off_vm + (g * TT + sl) * 4 : (g == kNG ? off_sc : off_pos) + sl * 4;
+            *reinterpret_cast<uint32_t*>(pg + o) = *reinterpret_cast<const uint32_t*>(img + o);
+        }
+#pragma unroll
+        for (int i = 0; i < (kVBytes + 1023) / 1024; ++i) {
+            const int o = off_vc + 1024 * i + 16 * lane;
+            if (1024 * i + 16 * lane >= kVBytes) break;
+            const uint4 v = *reinterpret_cast<const uint4*>(img + o);
+            *reinterpret_cast<uint4*>(pg + o) = make_uint4(v.x | vold[i].x, v.y | vold[i].y, v.z | vold[i].z, v.w | vold[i].w);
+        }
+    }
+    wave_lds_sync();  // the image is reused by the wave's next job
 }
 
 // One page job in the page format of its section (the layouts' formats; see
 // kLayoutFmts), so that row widths and bit positions are constants.
-__device__ __forceinline__ void commit_job(const AppendArgs& a, const JobDesc& s_job,
-                                           uint32_t (*s_rows)[kWave][kRowWords])
+__device__ __forceinline__ void commit_job(const AppendArgs& a, const JobDesc& job, PageImage& img)
 {
-    const int sec = __builtin_amdgcn_readfirstlane(s_job.sec);
+    const int sec = job.sec;
     const int kb = a.kb[sec], vb = a.vb[sec], T = a.T[sec];
-    if (kb == 8 && vb == 4) commit_job_fmt<8, 4, 16>(a, s_job, s_rows);
-    else if (kb == 4 && vb == 2 && T == 32) commit_job_fmt<4, 2, 32>(a, s_job, s_rows);
-    else if (kb == 8 && vb == 8) commit_job_fmt<8, 8, 16>(a, s_job, s_rows);
-    else if (kb == 8 && vb == 2) commit_job_fmt<8, 2, 16>(a, s_job, s_rows);
-    else if (kb == 4 && vb == 1) commit_job_fmt<4, 1, 32>(a, s_job, s_rows);
-    else commit_job_fmt<4, 2, 16>(a, s_job, s_rows);
+    if (kb == 8 && vb == 4) commit_job_fmt<8, 4, 16>(a, job, img);
+    else if (kb == 4 && vb == 2 && T == 32) commit_job_fmt<4, 2, 32>(a, job, img);
+    else if (kb == 8 && vb == 8) commit_job_fmt<8, 8, 16>(a, job, img);
+    else if (kb == 8 && vb == 2) commit_job_fmt<8, 2, 16>(a, job, img);
+    else if (kb == 4 && vb == 1) commit_job_fmt<4, 1, 32>(a, job, img);
+    else commit_job_fmt<4, 2, 16>(a, job, img);
+}
+
+// A table's state before the call, t uniform: through scalar loads (the
+// classify kernel wrote it; no kernel that reads it writes it).
+__device__ __forceinline__ TState uniform_state(const TState* ts, int t)
+{
+    typedef const __attribute__((address_space(4))) int32_t* cptr;
+    const cptr p = (cptr)(ts + t);
+    TState s;
+    s.cnt[0] = p[0];
+    s.cnt[1] = p[1];
+    s.lold[0] = p[2];
+    s.lold[1] = p[3];
+    s.pold[0] = p[4];
+    s.pold[1] = p[5];
+    s.ring_off = p[6];
+    s.n = p[7];
+    return s;
 }
 
 constexpr int kPlanKeep = 2;  // tables per thread whose state stays in registers
 
-__global__ __launch_bounds__(kCommitThreads) void append_commit(AppendArgs a)
+__global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(AppendArgs a)
 {
     const int tid = threadIdx.x;
     const int NT = a.B * a.Hkv;
     const int P = a.p_max;
     __shared__ long long s_scan[kCommitThreads / kWave];
     __shared__ uint32_t s_bits[kCommitThreads / kWave];
-    __shared__ JobDesc s_job;
-    __shared__ uint32_t s_rows[kQuantWaves][kWave][kRowWords];
+    __shared__ long long s_pre[kAppendPlanTables];  // exclusive prefix of every table's plan word
+    __shared__ PageImage s_img[kQuantWaves];
     const long long head_old = a.flags->head_old, tail_old = a.flags->tail_old;
 
     // ---- the plan, in every workgroup (each thread a contiguous run of tables)
@@ -619,24 +651,30 @@ __global__ __launch_bounds__(kCommitThreads) void append_commit(AppendArgs a)
         if (tid == 0) a.ring_ptr[0] = head_old + total_need;
     }
 
-    // ---- page jobs ------------------------------------------------------------
-    for (int job = blockIdx.x; job < njobs; job += gridDim.x) {
-        // the thread whose run of tables holds this job describes it
-        const int run_first = (int)(before >> 32);
-        if (run_first <= job && job < run_first + (int)(packed >> 32)) {
-            long long pre = before;
-            for_tables([&](int t, const TState& s) {
-                if (s.n < 0) return;
-                const TablePlan tp = table_plan(s, P, a.tsh);
-                const int jo = (int)(pre >> 32);
-                if (jo <= job && job < jo + tp.jobs[0] + tp.jobs[1])
-                    describe_job(s_job, t, s, tp, pre, job, P, head_old, a.tsh);
-                pre += plan_word(tp);
-            });
-        }
-        __syncthreads();
-        commit_job(a, s_job, s_rows);
-        if (job + (int)gridDim.x < njobs) __syncthreads();  // s_job and s_rows are reused by the next job
+    // ---- page jobs, one per wave at a time --------------------------------------
+    {
+        long long pre = before;
+        for_tables([&](int t, const TState& s) {
+            s_pre[t] = pre;
+            pre += plan_word(table_plan(s, P, a.tsh));
+        });
+    }
+    __syncthreads();
+    const int lane = lane_id();
+    const int stride = (NT + kWave - 1) / kWave;
+    for (int job = (int)blockIdx.x * kQuantWaves + wave_index(); job < njobs; job += (int)gridDim.x * kQuantWaves) {
+        // the job's table is the last whose first job is <= job (tables without
+        // jobs share their successor's prefix): among every stride-th table,
+        // then among the stride tables from that one on
+        const int p0 = lane * stride;
+        const int blk = __popcll(__builtin_amdgcn_ballot_w64(p0 < NT && (int)(s_pre[p0 < NT ? p0 : 0] >> 32) <= job)) - 1;
+        const int p1 = blk * stride + lane;
+        const bool in = lane < stride && p1 < NT;
+        const int t = blk * stride + __popcll(__builtin_amdgcn_ballot_w64(in && (int)(s_pre[in ? p1 : 0] >> 32) <= job)) - 1;
+        const TState s = uniform_state(a.tstate, t);
+        JobDesc d;
+        describe_job(d, t, s, table_plan(s, P, a.tsh), read_lane<long long>(s_pre[t], 0), job, P, head_old, a.tsh);
+        commit_job(a, d, s_img[wave_index()]);
     }
 }
 
@@ -745,22 +783,18 @@ __global__ __launch_bounds__(kPlanThreads) void append_plan(AppendArgs a)
     }
 }
 
-__global__ __launch_bounds__(kCommitThreads) void append_commit_planned(AppendArgs a)
+__global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit_planned(AppendArgs a)
 {
-    __shared__ JobDesc s_job;
-    __shared__ uint32_t s_rows[kQuantWaves][kWave][kRowWords];
+    __shared__ PageImage s_img[kQuantWaves];
     if (!a.flags->ok) return;
     const int njobs = a.flags->njobs;
     const long long head_old = a.flags->head_old;
-    for (int job = blockIdx.x; job < njobs; job += gridDim.x) {
-        if (threadIdx.x == 0) {
-            const int t = a.job_table[job];
-            const TState s = a.tstate[t];
-            describe_job(s_job, t, s, table_plan(s, a.p_max, a.tsh), a.tplan[t], job, a.p_max, head_old, a.tsh);
-        }
-        __syncthreads();
-        commit_job(a, s_job, s_rows);
-        if (job + (int)gridDim.x < njobs) __syncthreads();  // s_job and s_rows are reused by the next job
+    for (int job = (int)blockIdx.x * kQuantWaves + wave_index(); job < njobs; job += (int)gridDim.x * kQuantWaves) {
+        const int t = __builtin_amdgcn_readfirstlane(a.job_table[job]);
+        const TState s = uniform_state(a.tstate, t);
+        JobDesc d;
+        describe_job(d, t, s, table_plan(s, a.p_max, a.tsh), read_lane<long long>(a.tplan[t], 0), job, a.p_max, head_old, a.tsh);
+        commit_job(a, d, s_img[wave_index()]);
     }
 }
 
@@ -794,7 +828,7 @@ __global__ __launch_bounds__(kCommitThreads) void append_one(AppendArgs a)
     __shared__ long long s_scan[kCommitThreads / kWave];
     __shared__ uint32_t s_bits[kCommitThreads / kWave];
     __shared__ JobDesc s_job;
-    __shared__ uint32_t s_rows[kQuantWaves][kWave][kRowWords];
+    __shared__ PageImage s_img;
     __shared__ int s_off[kAppendPlanTables];  // row offset of each sequence (new tokens of the lower ones)
     __shared__ int s_job_here, s_last;
     const unsigned long long tag = call_tag();
@@ -915,7 +949,22 @@ __global__ __launch_bounds__(kCommitThreads) void append_one(AppendArgs a)
         }
     }
     __syncthreads();
-    if (s_job_here) commit_job(a, s_job, s_rows);
+    if (s_job_here && wave_index() == 0) {
+        JobDesc d;
+        d.t = __builtin_amdgcn_readfirstlane(s_job.t);
+        d.sec = __builtin_amdgcn_readfirstlane(s_job.sec);
+        d.p = __builtin_amdgcn_readfirstlane(s_job.p);
+        d.u0 = __builtin_amdgcn_readfirstlane(s_job.u0);
+        d.u1 = __builtin_amdgcn_readfirstlane(s_job.u1);
+        d.lold = __builtin_amdgcn_readfirstlane(s_job.lold);
+        d.n = __builtin_amdgcn_readfirstlane(s_job.n);
+        d.tslot = __builtin_amdgcn_readfirstlane(s_job.tslot);
+        d.ring_idx = read_lane<long long>(s_job.ring_idx, 0);
+        d.one = 1;
+        d.off_b = __builtin_amdgcn_readfirstlane(s_job.off_b);
+        d.sold = __builtin_amdgcn_readfirstlane(s_job.sold);
+        commit_job(a, d, s_img);
+    }
 
     // ---- the workgroup arriving last writes the state after the call
     __syncthreads();

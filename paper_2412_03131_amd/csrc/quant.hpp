@@ -1,6 +1,8 @@
-// quant.hpp -- the group quantizer of Sec. 2.2 as the append and the
-// generation-phase kernels run it: one 32-dim group spread over a 16-lane row,
-// two values per lane, bit-exact with the IEEE fp32 definition.
+// quant.hpp -- the group quantizer of Sec. 2.2, bit-exact with the IEEE fp32
+// definition, in two mappings: one 32-dim group over a 16-lane row, two values per
+// lane (quant_pair: the generation step, one token per wave), and over a quad,
+// eight values per lane (quant_oct: the append's page jobs, four tokens per wave
+// at a time; the group's extremes and scale cost a quarter per value).
 #pragma once
 
 #include "common.hpp"
@@ -72,6 +74,75 @@ __device__ __forceinline__ void quant_pair(uint32_t xbits, int lb, uint32_t& sz,
         codes_of(x0 - z, x1 - z, s, (float)lb, c0, c1);
     }
     sz = s16 | (z16 << 16);
+}
+
+// RN(d / LB) for the code ranges LB = 1, 3, 15, 255 from RN(1 / LB): one Newton
+// step on the rounded product, which gives the IEEE quotient for every 24-bit
+// d (checked for all significands of each LB; d is 0 or at least 2^-24, so nothing
+// underflows).  Infinities and NaN pass through as they do in a division.
+template <int LB>
+__device__ __forceinline__ float div_by_range(float d)
+{
+#pragma clang fp contract(off)
+    if constexpr (LB == 1) return d;
+    constexpr float y = 1.0f / (float)LB;
+    const float q0 = d * y;
+    const float q = __builtin_fmaf(__builtin_fmaf(-(float)LB, q0, d), y, q0);
+    return d < INFINITY ? q : d;
+}
+
+typedef _Float16 q_half2 __attribute__((ext_vector_type(2)));
+
+template <int CTRL>
+__device__ __forceinline__ q_half2 dpp_h2(q_half2 x)
+{
+    return __builtin_bit_cast(q_half2, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+
+// Quantize one 32-dim group spread over a quad of lanes, eight consecutive
+// values each (four fp16 pairs), to codes 0 .. LB, as floats.  The arithmetic
+// is quant_pair's: extremes (exact in fp16), s = fp16((max - min) / LB),
+// z = fp16(min), code = clamp(rint((x - z) / s)) with the quotient through the
+// hardware reciprocal and divided exactly within 2^-12 of a half-integer (the
+// clamp comes first: its bounds are integers, so it commutes with the
+// rounding, and x >= z).
+template <int LB>
+__device__ __forceinline__ void quant_oct(const uint4& x, uint32_t& sz, float (&code)[8])
+{
+#pragma clang fp contract(off)
+    const q_half2 a = __builtin_bit_cast(q_half2, x.x), b = __builtin_bit_cast(q_half2, x.y);
+    const q_half2 c = __builtin_bit_cast(q_half2, x.z), d = __builtin_bit_cast(q_half2, x.w);
+    q_half2 lo = __builtin_elementwise_min(__builtin_elementwise_min(a, b), __builtin_elementwise_min(c, d));
+    q_half2 hi = __builtin_elementwise_max(__builtin_elementwise_max(a, b), __builtin_elementwise_max(c, d));
+    lo = __builtin_elementwise_min(lo, dpp_h2<0xB1>(lo));  // quad_perm [1,0,3,2]
+    hi = __builtin_elementwise_max(hi, dpp_h2<0xB1>(hi));
+    lo = __builtin_elementwise_min(lo, dpp_h2<0x4E>(lo));  // quad_perm [2,3,0,1]
+    hi = __builtin_elementwise_max(hi, dpp_h2<0x4E>(hi));
+    const float mn = fminf((float)lo.x, (float)lo.y) + 0.0f;  // -0 counts as +0
+    const float mx = fmaxf((float)hi.x, (float)hi.y) + 0.0f;
+    const uint32_t s16 = f2h_rne(div_by_range<LB>(mx - mn));
+    const uint32_t z16 = f2h_rne(mn);
+    const float s = h2f(s16), z = h2f(z16);
+    const float rs = s16 == 0 ? 0.0f : __builtin_amdgcn_rcpf(s);  // scale 0: every code 0
+    sz = s16 | (z16 << 16);
+    const float v[8] = {(float)a.x, (float)a.y, (float)b.x, (float)b.y, (float)c.x, (float)c.y, (float)d.x, (float)d.y};
+    float q[8], far = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        q[i] = __builtin_amdgcn_fmed3f((v[i] - z) * rs, 0.0f, (float)LB);
+        code[i] = rintf(q[i]);
+        far = fmaxf(far, fabsf(q[i] - code[i]));
+    }
+    if (far > 0.5f - 0x1p-12f) {
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (fabsf(q[i] - code[i]) > 0.5f - 0x1p-12f) {
+                asm volatile("" ::: "memory");
+                code[i] = fminf(rintf((v[i] - z) / s), (float)LB);
+            }
+        }
+    }
 }
 
 }  // namespace dkv

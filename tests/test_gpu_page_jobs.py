@@ -1,0 +1,57 @@
+"""Page jobs of the append, one wave per page: fresh and continued pages with the job's
+slots starting and ending anywhere (each lane row's first and last slot, one slot, a whole
+page), every page format, and groups at the quantizer's edges.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+from gpu_util import assert_state_equal, dev_cache_from_oracle, layouts, t
+
+from oracle import oracle as orc
+from paper_2412_03131_amd import diffkv as dk
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = [dict(), dict(v_bits=(8, 2)), dict(v_bits=(2, 1)), dict(tokens_per_page=(16, 16))]
+
+
+def edge_values(rng, rows, Hkv):
+    """Groups of 32: plain, constant, ranges whose scale rounds to zero or a subnormal, signed
+    zeros, the largest finite values, and quotients at or next to half-integers."""
+    x = rng.standard_normal((rows, Hkv, 4, 32)).astype(np.float32)
+    kind = rng.integers(0, 8, (rows, Hkv, 4))
+    x[kind == 1] = np.float32(1.5)
+    tiny = rng.integers(0, 40, x.shape).astype(np.float32) * np.float32(2.0 ** -24)
+    x[kind == 2] = tiny[kind == 2]
+    x[kind == 3] = np.where(rng.random(x.shape) < 0.5, np.float32(-0.0), np.float32(0.0))[kind == 3]
+    x[kind == 4] = np.where(rng.random(x.shape) < 0.5, np.float32(-65504), np.float32(65504))[kind == 4]
+    grid = rng.integers(0, 511, x.shape).astype(np.float32) * np.float32(0.5)
+    grid[..., 0], grid[..., 1] = 0.0, 255.0
+    x[kind == 5] = grid[kind == 5]
+    grid = rng.integers(0, 31, x.shape).astype(np.float32) * np.float32(0.25) - np.float32(2.0)
+    grid[..., 0], grid[..., 1] = -2.0, 5.5
+    x[kind == 6] = grid[kind == 6]
+    return x.astype(np.float16).view(np.uint16).reshape(rows, Hkv, 128)
+
+
+@pytest.mark.parametrize("layout", range(4))
+@pytest.mark.parametrize("B,Hkv", [(5, 3), (70, 15)])  # the plan in every workgroup, and planned once
+def test_page_jobs_bitexact(layout, B, Hkv):
+    rng = np.random.default_rng(300 + layout)
+    Lo, Ld = layouts(max_seq_len=192, **LAYOUTS[layout])
+    pages = B * Hkv * 16
+    oc = orc.Cache(Lo, pages, B, Hkv, ring=rng.permutation(pages))
+    oc.pool[:] = rng.integers(0, 256, oc.pool.shape, dtype=np.uint8)  # free pages hold old bytes
+    dc = dev_cache_from_oracle(Ld, oc)
+    for step, most in enumerate((40, 3, 17, 1, 35, 5)):
+        new_len = rng.integers(0, most + 1, B).astype(np.int32)
+        new_len[0] = most
+        rows = int(new_len.sum())
+        k, v = edge_values(rng, rows, Hkv), edge_values(rng, rows, Hkv)
+        score = rng.random((rows, Hkv)).astype(np.float32)
+        hi = (new_len[:, None] * rng.random((B, Hkv))).astype(np.int32)
+        lo = ((new_len[:, None] - hi) * rng.choice([0.0, 0.5, 1.0], (B, Hkv))).astype(np.int32)
+        quota = np.stack([hi, lo], axis=2).astype(np.int32)
+        print("case: page jobs layout=%d B=%d step=%d" % (layout, B, step), flush=True)
+        orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+        dk.quantize_append(dc, t(new_len), t(k), t(v), t(score), quota=t(quota), total_new=rows, max_new=most)
+        assert oc.status[0] == 0
+        assert_state_equal(dc, oc, what="layout %d step %d" % (layout, step))
