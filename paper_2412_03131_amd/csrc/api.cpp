@@ -161,9 +161,10 @@ AttnWs attn_ws(int64_t B, int64_t Hq, int64_t Hkv, int64_t splits, int64_t worke
     return w;
 }
 
-// Prompt significance: sequence offsets and clamped lengths, row log2-sum-exps.
+// Prompt significance: sequence offsets and clamped lengths, work counters, row log2-sum-exps,
+// the column pass's sums per query segment.
 struct PromptWs {
-    int64_t off, nlen, lse2, total;
+    int64_t off, nlen, ctr, lse2, part, total;
 };
 
 PromptWs prompt_ws(int64_t B, int64_t Hq, int64_t total_new)
@@ -172,7 +173,9 @@ PromptWs prompt_ws(int64_t B, int64_t Hq, int64_t total_new)
     int64_t o = 0;
     w.off = o;  o = align256(o + B * 8);
     w.nlen = o; o = align256(o + B * 4);
+    w.ctr = o;  o = align256(o + 64);
     w.lse2 = o; o = align256(o + total_new * Hq * 4);
+    w.part = o; o = align256(o + prompt_part_rows(B, Hq, total_new) * 4);
     w.total = o;
     return w;
 }
@@ -439,6 +442,9 @@ diffkv_status diffkv_prompt_significance(const diffkv_layout* layout, int32_t nu
     uint8_t* base = static_cast<uint8_t*>(ws);
     a.off = reinterpret_cast<long long*>(base + w.off);
     a.nlen = reinterpret_cast<int32_t*>(base + w.nlen);
+    a.ctr = reinterpret_cast<int*>(base + w.ctr);
+    a.segs = prompt_segs(num_seqs, num_kv_heads, total_new);
+    a.part = reinterpret_cast<float*>(base + w.part);
     a.lse2 = reinterpret_cast<float*>(base + w.lse2);
     hipError_t e = launch_prompt_significance(a, num_q_heads / num_kv_heads, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? DIFFKV_OK : DIFFKV_E_LAUNCH;

@@ -184,7 +184,34 @@ struct PromptArgs {
     long long* off;      // [B] first row of each sequence (workspace)
     int32_t* nlen;       // [B] rows of each sequence, clamped to max_new and total_new (workspace)
     float* lse2;         // [total_new][Hq] row log2-sum-exp (workspace)
+    int* ctr;            // [16] work counters of the two passes (workspace)
+    int segs;            // query segments per key block of the column pass
+    float* part;         // [segs][total_new][Hkv] the segments' sums, segs > 1 (workspace)
 };
+
+// Query segments per 256-key block of the column pass: where there are fewer key
+// blocks than would keep the device busy, each block's queries are cut, down to
+// eight ways (the first block of one 4999-token prompt holds an eightieth of the
+// work of its 160 blocks, so the pass took as long as that one block: 867 us at 64
+// query heads, 296 us cut).  A sum over segments replaces the direct store.
+constexpr int kPromptBusyBlocks = 2048;
+constexpr int kPromptMaxSegs = 8;
+inline int prompt_segs(long long B, long long Hkv, long long total_new)
+{
+    const long long blocks = (total_new / 256 + B) * Hkv;
+    if (blocks <= 0) return 1;
+    const long long s = (kPromptBusyBlocks + blocks - 1) / blocks;
+    return (int)(s < kPromptMaxSegs ? s : kPromptMaxSegs);
+}
+// Most values the segments' sums take for any number of KV heads (Hq / 8 .. Hq):
+// the workspace size is not told it.
+inline long long prompt_part_rows(long long B, long long Hq, long long total_new)
+{
+    const long long per_head = total_new / 256 + B;
+    if (per_head <= 0 || per_head * ((Hq + 7) / 8) >= kPromptBusyBlocks) return 0;
+    const long long cut = kPromptBusyBlocks / per_head + 1 + Hq, all = kPromptMaxSegs * Hq;
+    return total_new * (cut < all ? cut : all);
+}
 hipError_t launch_prompt_significance(const PromptArgs& a, int g, hipStream_t st);
 
 // Fixed device scratch of diffkv_decode_attention_noalloc, one per device.

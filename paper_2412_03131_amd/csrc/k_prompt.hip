@@ -3,32 +3,39 @@
 // Token p of an N-token prompt is scored by the mean, over the queries
 // j = p..N-1, of the causal softmax probability query j gives it, the KV
 // head's g query heads combined by their maximum per query.  Two passes over
-// the prompt's fp16 q and k, both built on v_mfma_f32_16x16x32_f16 tiles
+// the prompt's fp16 q and k, both built on v_mfma_f32_32x32x16_f16 tiles
 // (fp16 products, exact in fp32, fp32 sums):
 //
-//   ps_rows  per (sequence, KV head, block of query positions): the log2-sum-
-//            exp of every query row of the group's heads over keys 0..j.  The
-//            queries sit in registers as MFMA B operands (all g heads of 16
-//            positions per wave, more positions when g is small so that every
-//            key fragment read from LDS feeds at least four MFMAs); key blocks
-//            of 64 rows are staged through LDS, double buffered, the next one
-//            fetched into registers while the current one is multiplied.  The
-//            running max is raised lazily (only when a row's new logits pass
-//            it by more than 2^8, a wave-uniform branch), so most key tiles
-//            cost one exp per logit and no rescale.
-//   ps_cols  per (sequence, KV head, block of 256 keys): the keys sit in
-//            registers as A operands (64 per wave); tiles of 16 query
-//            positions x g heads, with their row log2-sum-exps, are staged
-//            through LDS.  Per (key, query) the g logits are reduced by max
-//            after subtracting each head's row normalizer, so one exp2 gives
-//            the group's maximum probability; column sums stay per lane until
-//            a single cross-lane reduction at the end, so no atomics and a
-//            fixed summation order.
+//   ps_rows  per (sequence, KV head, 64 query positions): the log2-sum-exp of
+//            every query row of the group's heads over keys 0..j.  A wave holds
+//            64 queries of one head in registers as MFMA B operands; blocks of
+//            64 keys pass through LDS as A operands, so a tile's sixteen logits
+//            per lane belong to one query and their sum needs no exchange.  The
+//            running max is raised only when a tile's sum passes 2^8 (a
+//            wave-uniform branch; a far larger bound would not overflow, but the
+//            largest exponents would be rounded at their own size), so a logit
+//            costs one fma, one exp2, one add.
+//   ps_cols  per (sequence, KV head, 256 keys): 64 keys per wave in registers
+//            as B operands; tiles of 32 query positions x up to four heads pass
+//            through LDS as A operands.  Each tile's accumulation starts at its
+//            rows' -lse / c (read from LDS into the accumulator), so the
+//            maximum over the heads needs nothing per head and one exp2 gives
+//            the group's probability; a lane's sixteen values belong to one
+//            key, whose sum stays in the lane to the end: no atomics, a fixed
+//            order.  Few key blocks are cut into query segments (prompt_segs).
 //
-// Work order: the blocks of one (sequence, KV head) are numbered contiguously
-// and mapped to one XCD (consecutive workgroups go round-robin over the 8
-// XCDs), so that the key and query tiles they re-read stay in that XCD's L2;
-// within a pair the heaviest blocks start first.
+// Both stage the next tile while they compute one, by loads with an LDS
+// destination.  The MFMA results stay in VGPRs (two or three waves per SIMD
+// bound the registers to 256; with more, every result went through an AGPR
+// copy).
+//
+// Bound by the matrix cores and, in the row pass, VALU issue about equally (one
+// exp2 is two slots): 64 prompts of 1k-4k tokens at 32 / 8 heads, 2 x 1.73
+// TFLOP, take 2.0 + 1.95 ms, 870 TFLOP/s, where a large library fp16 product
+// reaches 1260 on the device.  With 16x16 tiles through AGPRs, register-staged
+// and one workgroup per block it was 2.7 + 2.8 ms; of that, the 32x32 tiles
+// gave 0.4 and 0.1, work queues instead of workgroups per block (below) 0.3
+// and 0.6.
 
 #include "internal.hpp"
 
@@ -38,44 +45,142 @@ namespace {
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
 
-constexpr int kPsThreads = 256;         // 4 waves
+constexpr int kPsThreads = 256;         // 4 waves (offsets and column pass)
 constexpr int kKeyBlock = 64;           // keys per LDS stage of the row pass
 constexpr int kColKeys = 256;           // keys per workgroup of the column pass (64 per wave)
-constexpr int kRowChunks = 17;          // 16-byte chunks per LDS row: 128 halfs + 16 B pad
-constexpr float kSlack = 8.0f;          // lazy-max slack of the row pass (log2 units)
+constexpr int kChunks = 16;             // 16-byte chunks of a 128-half row
+constexpr float kRaise = 0x1p8f;        // row pass: a tile's sum past this raises the running max
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Row pass: a wave takes 64 query positions of one head, a workgroup all heads
+// of kPos positions, or half of seven or eight heads (four waves for one or two
+// heads, one wave per head above).  158 VGPRs: three waves per SIMD.
 template <int G>
-struct PsShape {
-    static constexpr int QI = G <= 4 ? 32 : 16;      // query positions per LDS stage of the column pass
-    static constexpr int QT = G >= 3 ? 1 : 4 / G;   // 16-position query tiles per head per wave
-    static constexpr int PW = 16 * QT;               // query positions per wave
-    static constexpr int PB = 4 * PW;                // query positions per workgroup
+struct RowShape {
+    static constexpr int kGroups = G >= 7 ? 2 : 1;               // head groups
+    static constexpr int kWaves = G <= 2 || G >= 7 ? 4 : G;
+    static constexpr int kPos = G <= 2 ? 64 * (4 / G) : 64;
+    static constexpr int kPerCu = 12 / kWaves;                   // resident workgroups per CU
 };
 
-__device__ __forceinline__ f4 mfma16(h8 a, h8 b, f4 c)
+// Column pass: a stage in LDS is kTiles tiles of 32 query positions x up to four
+// heads (groups of a tile's heads follow each other).
+template <int G>
+struct ColShape {
+    static constexpr int kGroups = (G + 3) / 4;
+    static constexpr int kHeads = (G + kGroups - 1) / kGroups;  // heads of a full group
+    static constexpr int kTiles = G == 1 ? 4 : (G == 2 ? 2 : 1);
+    static constexpr int kUnits = kTiles * kHeads;              // 32-row units of a stage
+};
+
+__device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-__device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
+// max(a, b) as the median of a, b and infinity: one instruction (fmaxf first
+// quiets an operand the compiler has not seen computed)
+__device__ __forceinline__ float max_med(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf()); }
 
-// Logical block of workgroup i among n: XCD x = i % 8 runs the logical range
-// [x * (n / 8) + min(x, n % 8), ...) in order.  A bijection of [0, n).
-__device__ __forceinline__ long long xcd_block(long long i, long long n)
-{
-    const long long per = n / 8, rem = n % 8, x = i % 8, k = i / 8;
-    return x * per + (x < rem ? x : rem) + k;
-}
+// Work items: (pair = sequence and KV head, block), handed out by eight counters,
+// one queue per XCD (consecutive workgroups go round-robin over the XCDs, so
+// workgroup i starts on queue i % 8; a queue that has run out passes it on to the
+// next).  Queue x holds pairs x, x + 8, ..., eight of them at a time, block-major
+// with the heaviest block (0) first: the blocks of a pair run close together and
+// share its rows in one XCD's L2, and every queue has pairs from all over the
+// batch.  The items vary by a factor of N in work, and workgroups are dispatched
+// strictly in order, over the shader engines in turn: one workgroup per item
+// kept 62 % of the waves resident (column pass, 64 prompts of 1k-4k tokens), so
+// each resident workgroup takes items until there are none.  Which workgroup
+// takes an item does not change its result.
+constexpr int kQueues = 8;
+constexpr int kQueuePairs = 8;
+struct WorkQueue {
+    int* ctr;      // [kQueues] items handed out
+    int x, tried;  // current queue, queues found empty
+    int pairs, nblk;
+    // next item of a nonempty block (live(pair, blk)), or false: one thread
+    template <typename Live>
+    __device__ __forceinline__ bool next(int& pair, int& blk, Live live)
+    {
+        while (tried < kQueues) {
+            const int np = (pairs - x + kQueues - 1) / kQueues;
+            const long long n = np > 0 ? (long long)np * nblk : 0;
+            const long long k = n > 0 ? atomicAdd(ctr + x, 1) : 0;
+            if (k >= n) {
+                x = (x + 1) % kQueues;
+                ++tried;
+                continue;
+            }
+            const int g = (int)(k / (kQueuePairs * nblk)), rem = (int)(k - (long long)g * kQueuePairs * nblk);
+            const int w = min(kQueuePairs, np - g * kQueuePairs);
+            blk = rem / w;
+            pair = x + kQueues * (g * kQueuePairs + rem % w);
+            if (live(pair, blk)) return true;
+        }
+        return false;
+    }
+};
 
 __device__ __forceinline__ h8 zero8()
 {
     h8 z;
     for (int i = 0; i < 8; i++) z[i] = (_Float16)0.0f;
     return z;
+}
+
+// LDS rows of 16 chunks without padding (loads with an LDS destination write
+// consecutive lanes' chunks side by side): chunk c of row r sits at c ^ (r % 16),
+// so sixteen rows' reads of one chunk fall into different banks.
+__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ (row & (kChunks - 1)); }
+
+// Loads with an LDS destination: four rows of 256 bytes, lane l taking the chunk
+// that belongs at place l % 16 of row l / 16; the 1 KiB lands at lds.
+// By address per lane, or (load_rows_at) uniform address plus a lane's 32-bit
+// byte offset.
+__device__ __forceinline__ uint32_t lds_addr(const void* lds)
+{
+    return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)lds;
+}
+__device__ __forceinline__ void load_rows(const uint16_t* src, const void* lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr(lds)), "v"(src) : "memory");
+}
+__device__ __forceinline__ void load_rows_at(const uint16_t* src, uint32_t off, const void* lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr(lds)), "v"(off), "s"(src) : "memory");
+}
+// Rows 4 * part .. of a tile whose row r starts at base + r * stride (elements;
+// rows past `most` repeat it).  v0: the lane's byte offset for part 0, i.e. its
+// row l / 16 and place l % 16 (lane_offset); the swizzle of part p is an
+// exclusive or with its rows' upper two bits.
+__device__ __forceinline__ uint32_t lane_offset(long long stride)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    return (uint32_t)(lane >> 4) * (uint32_t)(stride * 2) + (uint32_t)((lane & 15) ^ (lane >> 4)) * 16;
+}
+constexpr long long kMaxStride = 1LL << 28;  // elements per row up to which lane_offset fits 32 bits
+__device__ __forceinline__ void load_part(const uint16_t* base, long long stride, int part, int most, uint32_t v0,
+                                          const void* lds)
+{
+    if (most >= 4 * part + 3 && stride <= kMaxStride) {
+        load_rows_at(base + 4 * part * stride, v0 ^ (uint32_t)((part & 3) << 6), lds);
+    } else {
+        const int lane = threadIdx.x & (kWave - 1);
+        int r = 4 * part + (lane >> 4);
+        asm volatile("" : "+v"(r));  // (computed here: the rare side's addresses stay out of the loops' registers)
+        load_rows(base + (long long)min(r, most) * stride + swz(r, lane & 15) * 8, lds);
+    }
+}
+// The loads above are seen by the workgroup: each wave waits for its own, then all meet.
+__device__ __forceinline__ void stage_ready()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 }
 
 }  // namespace
@@ -86,6 +191,7 @@ __global__ __launch_bounds__(kPsThreads) void ps_offsets(PromptArgs a)
 {
     __shared__ long long part[kPsThreads];
     const int tid = threadIdx.x;
+    if (tid < 2 * kQueues) a.ctr[tid] = 0;  // the passes' work queues
     const int per = (a.B + kPsThreads - 1) / kPsThreads;
     const int b0 = tid * per, b1 = min(a.B, b0 + per);
     long long s = 0;
@@ -109,251 +215,326 @@ __global__ __launch_bounds__(kPsThreads) void ps_offsets(PromptArgs a)
 }
 
 // Pass 1: lse2[row][hq] = log2 sum_{p <= j} exp2(scale_log2 * q_j . k_p).
+// One item: a pair's block of query positions (blk 0 the last, the heaviest).
 template <int G>
-__global__ __launch_bounds__(kPsThreads) void ps_rows(PromptArgs a)
+__device__ __forceinline__ void rows_item(const PromptArgs& a, h8 (&sk)[2][kKeyBlock][kChunks], int bh, int blk, int nqb)
 {
-    constexpr int QT = PsShape<G>::QT, PW = PsShape<G>::PW, PB = PsShape<G>::PB;
-    __shared__ h8 sk[2][kKeyBlock][kRowChunks];
-
-    const int nqb = (a.max_new + PB - 1) / PB;
-    const long long nblk = (long long)a.B * a.Hkv * nqb;
-    const long long lb = xcd_block(blockIdx.x, nblk);
-    const int bh = (int)(lb / nqb);
-    const int qb = nqb - 1 - (int)(lb - (long long)bh * nqb);
+    using R = RowShape<G>;
+    constexpr int kWaves = R::kWaves, PB = R::kPos;
+    const int qb = nqb - 1 - blk / R::kGroups, hg = blk % R::kGroups;
     const int b = bh / a.Hkv, h = bh - b * a.Hkv;
     const int N = a.nlen[b];
     const long long off = a.off[b];
     const int q0 = qb * PB;
-    if (q0 >= N) return;
 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = wave_index();
-    const int col = lane & 15, grp = lane >> 4;
-    const int wq0 = q0 + w * PW;
+    const int col = lane & 31, half = lane >> 5;
+    const int t = G == 1 ? 0 : (G == 2 ? (w & 1) : 4 * hg + w);
+    const int wq0 = q0 + (G == 1 ? 64 * w : (G == 2 ? 64 * (w >> 1) : 0));
     const float c = a.scale_log2;
+    const bool idle = wq0 >= N || t >= G;  // (uniform) this wave only stages keys
 
-    h8 qf[QT][G][4];
-    for (int qt = 0; qt < QT; qt++) {
-        const int j = wq0 + qt * 16 + col;
-        for (int t = 0; t < G; t++) {
-            const h8* src = reinterpret_cast<const h8*>(a.q + ((off + j) * a.Hq + h * G + t) * kD);
-            for (int s = 0; s < 4; s++) qf[qt][t][s] = j < N ? src[4 * s + grp] : zero8();
-        }
+    // B operands: 32 positions per block, k = 16 s + 8 half ..
+    h8 qf[2][8];
+    for (int cb = 0; cb < 2; cb++) {
+        const int j = wq0 + 32 * cb + col;
+        const h8* src = reinterpret_cast<const h8*>(a.q + ((off + j) * a.Hq + h * G + t) * kD);
+        for (int s = 0; s < 8; s++) qf[cb][s] = j < N && t < G ? src[2 * s + half] : zero8();
     }
-    float m[QT][G], sum[QT][G];
-    for (int qt = 0; qt < QT; qt++)
-        for (int t = 0; t < G; t++) {
-            m[qt][t] = -1e30f;
-            sum[qt][t] = 0.0f;
-        }
+    float m[2] = {-1e30f, -1e30f}, sum[2] = {0.0f, 0.0f};
 
     const int last = min(N, q0 + PB) - 1;
     const int nkb = last / kKeyBlock + 1;
-    constexpr int kPer = kKeyBlock * 16 / kPsThreads;    // 16-byte chunks staged per thread
-    const int srow = threadIdx.x / (16 / kPer), spart = threadIdx.x % (16 / kPer);
-    h8 pre[kPer];
-    auto fetch = [&](int kb) {
-        const int p = kb * kKeyBlock + srow;
-        const h8* src = reinterpret_cast<const h8*>(a.k + ((off + p) * a.Hkv + h) * kD) + spart * kPer;
-        for (int i = 0; i < kPer; i++) pre[i] = p < N ? src[i] : zero8();
+    const long long stride = (long long)a.Hkv * kD;
+    const uint32_t v0 = lane_offset(stride);
+    auto stage = [&](int kb) {  // (rows past the prompt repeat its last: masked)
+        const uint16_t* base = a.k + ((off + (long long)kb * kKeyBlock) * a.Hkv + h) * kD;
+#pragma unroll
+        for (int i = 0; i < (16 + kWaves - 1) / kWaves; i++) {
+            const int part = i * kWaves + w;
+            if (part < 16) load_part(base, stride, part, N - 1 - kb * kKeyBlock, v0, &sk[kb & 1][4 * part][0]);
+        }
     };
-    auto stash = [&](int buf) {
-        for (int i = 0; i < kPer; i++) sk[buf][srow][spart * kPer + i] = pre[i];
-    };
-    fetch(0);
-    stash(0);
-    __syncthreads();
+    stage(0);
     for (int kb = 0; kb < nkb; kb++) {
+        stage_ready();
+        if (kb + 1 < nkb) stage(kb + 1);
         const int buf = kb & 1;
-        if (kb + 1 < nkb) fetch(kb + 1);
-        const int kbase = kb * kKeyBlock;
-        // waves whose positions all precede the block skip it; a block whose last
-        // key passes the wave's first position needs the causal mask (which also
-        // removes keys >= N: those lie after every valid position)
-        if (kbase < wq0 + PW && wq0 < N) {
-            const bool need_mask = kbase + kKeyBlock - 1 > wq0;
-            for (int kt = 0; kt < kKeyBlock / 16; kt++) {
-                h8 af[4];
-                for (int s = 0; s < 4; s++) af[s] = sk[buf][kt * 16 + col][4 * s + grp];
-                const int key0 = kbase + kt * 16 + 4 * grp;
-                for (int qt = 0; qt < QT; qt++) {
-                    const int j = wq0 + qt * 16 + col;
-                    for (int t = 0; t < G; t++) {
-                        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                        for (int s = 0; s < 4; s++) acc = mfma16(af[s], qf[qt][t][s], acc);
-                        if (need_mask)
-                            for (int i = 0; i < 4; i++)
-                                if (key0 + i > j) acc[i] = -__builtin_huge_valf();
-                        const float bm = max3f(acc[0], acc[1], fmaxf(acc[2], acc[3])) * c;
-                        if (__builtin_amdgcn_ballot_w64(bm > m[qt][t] + kSlack)) {
-                            const float mn = fmaxf(m[qt][t], bm);
-                            sum[qt][t] *= fast_exp2(m[qt][t] - mn);
-                            m[qt][t] = mn;
-                        }
-                        const float nm = -m[qt][t];
-                        sum[qt][t] += (fast_exp2(fmaf(acc[0], c, nm)) + fast_exp2(fmaf(acc[1], c, nm))) +
-                                      (fast_exp2(fmaf(acc[2], c, nm)) + fast_exp2(fmaf(acc[3], c, nm)));
+#pragma unroll
+        for (int kt = 0; kt < 2; kt++) {
+            const int key0 = kb * kKeyBlock + 32 * kt;
+            // (uniform) all of the wave's positions precede the keys
+            if (key0 > wq0 + 63 || idle) continue;
+            h8 af[8];
+            for (int s = 0; s < 8; s++) af[s] = sk[buf][32 * kt + col][swz(col, 2 * s + half)];
+            f16v acc[2];
+#pragma unroll
+            for (int cb = 0; cb < 2; cb++) {
+                f16v z;
+                for (int i = 0; i < 16; i++) z[i] = 0.0f;
+                acc[cb] = mfma32(af[0], qf[cb][0], z);
+                for (int s = 1; s < 8; s++) acc[cb] = mfma32(af[s], qf[cb][s], acc[cb]);
+            }
+#pragma unroll
+            for (int cb = 0; cb < 2; cb++) {
+                const int jb = wq0 + 32 * cb;
+                // the diagonal (it also removes keys >= N: they lie after every valid
+                // position); the empty asm keeps the selects inside the branch
+                if (key0 + 31 > jb) {
+                    const int lim = jb + col - key0 - 4 * half;
+                    for (int i = 0; i < 16; i++) {
+                        float v = 8 * (i / 4) + i % 4 > lim ? -__builtin_huge_valf() : acc[cb][i];
+                        asm volatile("" : "+v"(v));
+                        acc[cb][i] = v;
                     }
                 }
+                auto tile_sum = [&]() {
+                    const float nm = -m[cb];
+                    float s0 = 0.0f, s1 = 0.0f;
+                    for (int i = 0; i < 16; i += 2) {
+                        s0 += fast_exp2(fmaf(acc[cb][i], c, nm));
+                        s1 += fast_exp2(fmaf(acc[cb][i + 1], c, nm));
+                    }
+                    return s0 + s1;
+                };
+                float ts = tile_sum();
+                if (__builtin_amdgcn_ballot_w64(!(ts <= kRaise))) {
+                    float mx = acc[cb][0];
+                    for (int i = 1; i < 16; i++) mx = fmaxf(mx, acc[cb][i]);
+                    const float mn = fmaxf(m[cb], mx * c);
+                    sum[cb] *= fast_exp2(m[cb] - mn);
+                    m[cb] = mn;
+                    ts = tile_sum();
+                }
+                sum[cb] += ts;
             }
         }
-        if (kb + 1 < nkb) stash(buf ^ 1);
-        __syncthreads();
     }
-    // combine the four row groups of each column (lanes col, col+16, col+32, col+48)
-    for (int qt = 0; qt < QT; qt++) {
-        const int j = wq0 + qt * 16 + col;
-        for (int t = 0; t < G; t++) {
-            float mx = fmaxf(m[qt][t], __shfl_xor(m[qt][t], 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            float sm = sum[qt][t] * fast_exp2(m[qt][t] - mx);
-            sm += __shfl_xor(sm, 16);
-            sm += __shfl_xor(sm, 32);
-            if (grp == 0 && j < N) a.lse2[(off + j) * a.Hq + h * G + t] = mx + __builtin_amdgcn_logf(sm);
+    // the two halves' keys of each position
+    for (int cb = 0; cb < 2; cb++) {
+        const int j = wq0 + 32 * cb + col;
+        const float mo = __shfl_xor(m[cb], 32), so = __shfl_xor(sum[cb], 32);
+        const float mx = fmaxf(m[cb], mo);
+        const float sm = sum[cb] * fast_exp2(m[cb] - mx) + so * fast_exp2(mo - mx);
+        if (half == 0 && j < N && t < G) a.lse2[(off + j) * a.Hq + h * G + t] = mx + __builtin_amdgcn_logf(sm);
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(RowShape<G>::kWaves * kWave, 3) void ps_rows(PromptArgs a)
+{
+    using R = RowShape<G>;
+    __shared__ h8 sk[2][kKeyBlock][kChunks];
+    __shared__ int s_item[2];
+    const int nqb = (a.max_new + R::kPos - 1) / R::kPos;
+    WorkQueue queue = {a.ctr, (int)(blockIdx.x % kQueues), 0, a.B * a.Hkv, nqb * R::kGroups};
+    for (;;) {
+        if (threadIdx.x == 0) {
+            int pair = -1, blk = 0;
+            const bool any = queue.next(pair, blk, [&](int p, int k) { return (nqb - 1 - k / R::kGroups) * R::kPos < a.nlen[p / a.Hkv]; });
+            s_item[0] = any ? pair : -1;
+            s_item[1] = blk;
         }
+        __syncthreads();
+        const int bh = __builtin_amdgcn_readfirstlane(s_item[0]), blk = __builtin_amdgcn_readfirstlane(s_item[1]);
+        if (bh < 0) return;
+        rows_item<G>(a, sk, bh, blk, nqb);
+        __syncthreads();  // s_item and the stages are written again
     }
 }
 
 // Pass 2: score[row][h] = (1 / (N - p)) sum_{j >= p} max_t exp2(scale_log2 * q_j,t . k_p - lse2[j][t]).
 template <int G>
-__global__ __launch_bounds__(kPsThreads) void ps_cols(PromptArgs a)
-{
-    constexpr int QI = PsShape<G>::QI;
-    constexpr int NR = G * QI * 16 / kPsThreads;     // 16-byte chunks of q staged per thread
-    __shared__ h8 sq[2][G][QI][kRowChunks];
-    __shared__ float sl[2][G][QI];
+struct ColLds {
+    h8 q[2][ColShape<G>::kUnits][32][kChunks];  // [stage][tile * heads + head][position]
+    float bias[2][ColShape<G>::kUnits][32];     // -lse / c of those rows
+};
 
-    const int nkb = (a.max_new + kColKeys - 1) / kColKeys;
-    const long long nblk = (long long)a.B * a.Hkv * nkb;
-    const long long lb = xcd_block(blockIdx.x, nblk);
-    const int bh = (int)(lb / nkb);
-    const int kb = (int)(lb - (long long)bh * nkb);
+// One item: a pair's block of 256 keys (kb 0 the heaviest) and a segment of its
+// query tiles.
+template <int G>
+__device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, int bh, int kb, int seg)
+{
+    using S = ColShape<G>;
+    constexpr int QI = 32 * S::kTiles;               // query positions per stage
     const int b = bh / a.Hkv, h = bh - b * a.Hkv;
     const int N = a.nlen[b];
     const long long off = a.off[b];
     const int k0 = kb * kColKeys;
-    if (k0 >= N) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = wave_index();
-    const int col = lane & 15, grp = lane >> 4;
+    const int col = lane & 31, half = lane >> 5;
     const int wk0 = k0 + w * 64;
     const float c = a.scale_log2;
     const float inv_c = 1.0f / c;
 
-    h8 kf[4][4];
-    for (int kt = 0; kt < 4; kt++) {
-        const int p = wk0 + kt * 16 + col;
+    // B operands: 32 keys per block, k = 16 s + 8 half ..
+    h8 kf[2][8];
+    for (int cb = 0; cb < 2; cb++) {
+        const int p = wk0 + 32 * cb + col;
         const h8* src = reinterpret_cast<const h8*>(a.k + ((off + p) * a.Hkv + h) * kD);
-        for (int s = 0; s < 4; s++) kf[kt][s] = p < N ? src[4 * s + grp] : zero8();
+        for (int s = 0; s < 8; s++) kf[cb][s] = p < N ? src[2 * s + half] : zero8();
     }
-    float cs[4][4];
-    for (int kt = 0; kt < 4; kt++)
-        for (int i = 0; i < 4; i++) cs[kt][i] = 0.0f;
+    float cs[2] = {0.0f, 0.0f};
 
-    const int nq = (N - k0 + QI - 1) / QI;
-    h8 pq[NR];
+    const int nq = (N - k0 + QI - 1) / QI;  // stages [it0, it1) of the segment's positions
+    const int it0 = (int)((long long)seg * nq / a.segs), it1 = (int)((long long)(seg + 1) * nq / a.segs);
     float pl = 0.0f;
-    auto fetch = [&](int it) {
+    const long long stride = (long long)a.Hq * kD;
+    const uint32_t v0 = lane_offset(stride);
+    // Stage s = it * kGroups + g: positions k0 + it * QI .., heads g * kHeads ..
+    auto heads_of = [](int g) { return min(S::kHeads, G - g * S::kHeads); };
+    auto stage = [&](int it, int g, int buf) {
         const int j0 = k0 + it * QI;
-        for (int r = 0; r < NR; r++) {
-            const int cidx = r * kPsThreads + tid;
-            const int row = cidx >> 4, pos = row / G, t = row - pos * G;
-            const int j = j0 + pos;
-            const h8* src = reinterpret_cast<const h8*>(a.q + ((off + j) * a.Hq + h * G + t) * kD);
-            pq[r] = j < N ? src[cidx & 15] : zero8();
+        const int nh = heads_of(g), h0 = g * S::kHeads;
+        // (the parts' addresses are formed anew: kept over the loop they spill)
+        long long step = stride;
+        asm volatile("" : "+s"(step));
+        const uint16_t* base = a.q + (off + j0) * step + (h * G + h0) * kD;
+#pragma unroll
+        for (int i = 0; i < 2 * S::kUnits; i++) {    // eight 1 KiB parts per unit
+            const int part = i * 4 + w, u = part >> 3, tile = u / S::kHeads, t = u - tile * S::kHeads;
+            if (t >= nh || j0 + 32 * tile >= N) continue;
+            // (positions past the prompt repeat its last: their bias is -inf)
+            load_part(base + 32 * tile * step + t * kD, step, part & 7, N - 1 - j0 - 32 * tile, v0, &lds.q[buf][u][4 * (part & 7)][0]);
         }
-        if (tid < QI * G) {
-            const int pos = tid / G, t = tid - pos * G;
-            const int j = j0 + pos;
-            const long long e = (off + j) * a.Hq + h * G + t;
-            pl = j >= N ? __builtin_huge_valf() : (a.lse ? a.lse[e] * kLog2e : a.lse2[e]);
-        }
-    };
-    auto stash = [&](int buf) {
-        for (int r = 0; r < NR; r++) {
-            const int cidx = r * kPsThreads + tid;
-            const int row = cidx >> 4, pos = row / G, t = row - pos * G;
-            sq[buf][t][pos][cidx & 15] = pq[r];
-        }
-        if (tid < QI * G) {
-            const int pos = tid / G, t = tid - pos * G;
-            sl[buf][t][pos] = pl;
+        if (tid < S::kUnits * 32) {
+            const int u = tid >> 5, tile = u / S::kHeads, t = u - tile * S::kHeads;
+            const int j = j0 + 32 * tile + (tid & 31);
+            const long long e = (off + j) * a.Hq + h * G + h0 + t;
+            pl = j >= N || t >= nh ? __builtin_huge_valf() : (a.lse ? a.lse[e] * kLog2e : a.lse2[e]);
         }
     };
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int it = 0; it < nq; it++) {
-        const int buf = it & 1;
-        if (it + 1 < nq) fetch(it + 1);
-        for (int sub = 0; sub < QI / 16; sub++) {
-            const int j0 = k0 + it * QI + sub * 16;
-            if (j0 + 15 < wk0 || wk0 >= N) continue;   // no query of the tile reaches the wave's keys
-            const bool diag = j0 < wk0 + 63;
-            // the MFMA accumulates onto -lse/c, so acc = S - lse/c and the maximum over the
-            // heads needs no per-head arithmetic; exp2(c * max) is the group's probability
-            f4 mx[4];
-            for (int t = 0; t < G; t += 2) {
-                const bool pair = t + 1 < G;
-                h8 bf0[4], bf1[4];
-                for (int s = 0; s < 4; s++) bf0[s] = sq[buf][t][sub * 16 + col][4 * s + grp];
-                if (pair)
-                    for (int s = 0; s < 4; s++) bf1[s] = sq[buf][t + 1][sub * 16 + col][4 * s + grp];
-                const float z0 = -sl[buf][t][sub * 16 + col] * inv_c;
-                const float z1 = pair ? -sl[buf][t + 1][sub * 16 + col] * inv_c : 0.0f;
-                for (int kt = 0; kt < 4; kt++) {
-                    f4 acc0 = {z0, z0, z0, z0};
-                    for (int s = 0; s < 4; s++) acc0 = mfma16(kf[kt][s], bf0[s], acc0);
-                    if (pair) {
-                        f4 acc1 = {z1, z1, z1, z1};
-                        for (int s = 0; s < 4; s++) acc1 = mfma16(kf[kt][s], bf1[s], acc1);
-                        for (int i = 0; i < 4; i++)
-                            mx[kt][i] = t == 0 ? fmaxf(acc0[i], acc1[i]) : max3f(mx[kt][i], acc0[i], acc1[i]);
-                    } else {
-                        for (int i = 0; i < 4; i++) mx[kt][i] = t == 0 ? acc0[i] : fmaxf(mx[kt][i], acc0[i]);
+    // last positions first: the key blocks of one (sequence, KV head), which run at
+    // about the same time on one XCD, then read the same queries together
+    if (it1 > it0) stage(it1 - 1, 0, 0);
+    int buf = 0;
+    for (int it = it1 - 1; it >= it0; it--) {
+        f16v mx[S::kTiles][2];
+#pragma unroll
+        for (int g = 0; g < S::kGroups; g++) {
+            if (tid < S::kUnits * 32) lds.bias[buf][tid >> 5][tid & 31] = -pl * inv_c;
+            stage_ready();
+            if (g + 1 < S::kGroups) stage(it, g + 1, buf ^ 1);
+            else if (it > it0) stage(it - 1, 0, buf ^ 1);
+#pragma unroll
+            for (int tile = 0; tile < S::kTiles; tile++) {
+                const int j0 = k0 + it * QI + 32 * tile;
+                if (j0 + 31 < wk0 || wk0 >= N || j0 >= N) continue;  // (uniform) no query of the tile reaches the wave's keys
+                // A operands: the tile's positions of one head; the accumulation starts at
+                // -lse/c, so the maximum over the heads needs no arithmetic per head
+#pragma unroll
+                for (int t = 0; t < S::kHeads; t++) {
+                    if (t >= heads_of(g)) break;
+                    const int u = tile * S::kHeads + t;
+                    h8 af[8];
+                    for (int s = 0; s < 8; s++) af[s] = lds.q[buf][u][col][swz(col, 2 * s + half)];
+                    f16v bias;
+                    for (int r = 0; r < 4; r++) {
+                        const f4 v = *reinterpret_cast<const f4*>(&lds.bias[buf][u][8 * r + 4 * half]);
+                        for (int i = 0; i < 4; i++) bias[4 * r + i] = v[i];
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < 2; cb++) {
+                        f16v acc = mfma32(af[0], kf[cb][0], bias);
+                        for (int s = 1; s < 8; s++) acc = mfma32(af[s], kf[cb][s], acc);
+                        if (g == 0 && t == 0) mx[tile][cb] = acc;
+                        else
+                            for (int i = 0; i < 16; i++) mx[tile][cb][i] = max_med(mx[tile][cb][i], acc[i]);
                     }
                 }
-            }
-            const int j = j0 + col;
-            for (int kt = 0; kt < 4; kt++)
-                for (int i = 0; i < 4; i++) {
-                    float v = fast_exp2(mx[kt][i] * c);
-                    if (diag && wk0 + kt * 16 + 4 * grp + i > j) v = 0.0f;
-                    cs[kt][i] += v;
+                if (g + 1 < S::kGroups) continue;
+#pragma unroll
+                for (int cb = 0; cb < 2; cb++) {
+                    const int p0 = wk0 + 32 * cb;
+                    if (j0 < p0 + 31) {  // the diagonal: queries before the key
+                        const int lim = p0 + col - j0 - 4 * half;
+                        for (int i = 0; i < 16; i++) {
+                            float v = 8 * (i / 4) + i % 4 < lim ? -__builtin_huge_valf() : mx[tile][cb][i];
+                            asm volatile("" : "+v"(v));
+                            mx[tile][cb][i] = v;
+                        }
+                    }
+                    float s0 = 0.0f, s1 = 0.0f;
+                    for (int i = 0; i < 16; i += 2) {
+                        s0 += fast_exp2(mx[tile][cb][i] * c);
+                        s1 += fast_exp2(mx[tile][cb][i + 1] * c);
+                    }
+                    cs[cb] += s0 + s1;
                 }
+            }
+            buf ^= 1;
         }
-        if (it + 1 < nq) stash(buf ^ 1);
-        __syncthreads();
     }
-    for (int kt = 0; kt < 4; kt++)
-        for (int i = 0; i < 4; i++) {
-            float v = cs[kt][i];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 8);
-            const int p = wk0 + kt * 16 + 4 * grp + i;
-            if (col == 0 && p < N) a.score[(off + p) * a.Hkv + h] = v / (float)(N - p);
+    for (int cb = 0; cb < 2; cb++) {
+        const float v = cs[cb] + __shfl_xor(cs[cb], 32);
+        const int p = wk0 + 32 * cb + col;
+        if (half == 0 && p < N) {
+            if (a.segs == 1) a.score[(off + p) * a.Hkv + h] = v / (float)(N - p);
+            else a.part[((long long)seg * a.total_new + off + p) * a.Hkv + h] = v;
         }
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(kPsThreads, 2) void ps_cols(PromptArgs a)
+{
+    __shared__ ColLds<G> lds;
+    __shared__ int s_item[2];
+    const int nkb = (a.max_new + kColKeys - 1) / kColKeys;
+    WorkQueue queue = {a.ctr + kQueues, (int)(blockIdx.x % kQueues), 0, a.B * a.Hkv, nkb * a.segs};
+    for (;;) {
+        if (threadIdx.x == 0) {
+            int pair = -1, blk = 0;
+            const bool any = queue.next(pair, blk, [&](int p, int k) { return k / a.segs * kColKeys < a.nlen[p / a.Hkv]; });
+            s_item[0] = any ? pair : -1;
+            s_item[1] = blk;
+        }
+        __syncthreads();
+        const int bh = __builtin_amdgcn_readfirstlane(s_item[0]), blk = __builtin_amdgcn_readfirstlane(s_item[1]);
+        if (bh < 0) return;
+        cols_item<G>(a, lds, bh, blk / a.segs, blk % a.segs);
+        __syncthreads();  // s_item and the stages are written again
+    }
+}
+
+// The segments' sums of each (row, KV head), in order, over the row's queries.
+__global__ __launch_bounds__(kPsThreads) void ps_finish(PromptArgs a)
+{
+    const int b = blockIdx.y;
+    const int N = a.nlen[b];
+    const long long n = (long long)N * a.Hkv, base = a.off[b] * a.Hkv, step = a.total_new * a.Hkv;
+    for (long long i = (long long)blockIdx.x * kPsThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kPsThreads) {
+        float v = 0.0f;
+        for (int s = 0; s < a.segs; s++) v += a.part[s * step + base + i];
+        a.score[base + i] = v / (float)(N - (int)(i / a.Hkv));
+    }
 }
 
 namespace {
 
 template <int G>
-hipError_t launch_prompt_g(const PromptArgs& a, hipStream_t st)
+hipError_t launch_prompt_g(const PromptArgs& a, int cus, hipStream_t st)
 {
+    const long long pairs = (long long)a.B * a.Hkv;
     hipError_t e;
     if (!a.lse) {
-        const long long nqb = (a.max_new + PsShape<G>::PB - 1) / PsShape<G>::PB;
-        const long long grid = (long long)a.B * a.Hkv * nqb;
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        if ((e = launch1(ps_rows<G>, (unsigned)grid, kPsThreads, st, a)) != hipSuccess) return e;
+        const long long items = pairs * ((a.max_new + RowShape<G>::kPos - 1) / RowShape<G>::kPos) * RowShape<G>::kGroups;
+        if (items > 0x7fffffffLL) return hipErrorInvalidValue;
+        const long long grid = min(items, (long long)cus * RowShape<G>::kPerCu);
+        if ((e = launch1(ps_rows<G>, (unsigned)grid, RowShape<G>::kWaves * kWave, st, a)) != hipSuccess) return e;
     }
-    const long long grid = (long long)a.B * a.Hkv * ((a.max_new + kColKeys - 1) / kColKeys);
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    return launch1(ps_cols<G>, (unsigned)grid, kPsThreads, st, a);
+    const long long items = pairs * ((a.max_new + kColKeys - 1) / kColKeys) * a.segs;
+    if (items > 0x7fffffffLL) return hipErrorInvalidValue;
+    e = launch1(ps_cols<G>, (unsigned)min(items, (long long)cus * 2), kPsThreads, st, a);
+    if (e != hipSuccess || a.segs == 1) return e;
+    const long long rows = (long long)a.max_new * a.Hkv;
+    const unsigned gx = (unsigned)min((rows + kPsThreads - 1) / kPsThreads, 64LL);
+    void* args[] = {const_cast<PromptArgs*>(&a)};
+    return hipLaunchKernel(reinterpret_cast<const void*>(ps_finish), dim3(gx, (unsigned)a.B), dim3(kPsThreads), args, 0, st);
 }
 
 }  // namespace
@@ -361,17 +542,22 @@ hipError_t launch_prompt_g(const PromptArgs& a, hipStream_t st)
 hipError_t launch_prompt_significance(const PromptArgs& a, int g, hipStream_t st)
 {
     if (a.B <= 0 || a.max_new <= 0) return hipSuccess;
-    hipError_t e = launch1(ps_offsets, 1, kPsThreads, st, a);
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (cus < 1) cus = 1;
+    e = launch1(ps_offsets, 1, kPsThreads, st, a);
     if (e != hipSuccess) return e;
     switch (g) {
-    case 1: return launch_prompt_g<1>(a, st);
-    case 2: return launch_prompt_g<2>(a, st);
-    case 3: return launch_prompt_g<3>(a, st);
-    case 4: return launch_prompt_g<4>(a, st);
-    case 5: return launch_prompt_g<5>(a, st);
-    case 6: return launch_prompt_g<6>(a, st);
-    case 7: return launch_prompt_g<7>(a, st);
-    case 8: return launch_prompt_g<8>(a, st);
+    case 1: return launch_prompt_g<1>(a, cus, st);
+    case 2: return launch_prompt_g<2>(a, cus, st);
+    case 3: return launch_prompt_g<3>(a, cus, st);
+    case 4: return launch_prompt_g<4>(a, cus, st);
+    case 5: return launch_prompt_g<5>(a, cus, st);
+    case 6: return launch_prompt_g<6>(a, cus, st);
+    case 7: return launch_prompt_g<7>(a, cus, st);
+    case 8: return launch_prompt_g<8>(a, cus, st);
     default: return hipErrorInvalidValue;
     }
 }
