@@ -29,7 +29,12 @@ constexpr int kPairMaxGq = 5;
 constexpr int kModePair = -2;  // launch mode of attn_pair (internal; never a caller's num_splits)
 constexpr int kPartStride = kD + 2;
 constexpr int kSigWaves = 4;
-constexpr int kSigPages = 16;  // pages per workgroup of attn_significance
+// attn_significance: pages per working workgroup, and how many workgroups a call
+// launches at most (beyond one per table).  One workgroup per sixteen pages of the
+// longest table there can be was 17k workgroups for 512 tables of 72 pages, two
+// thirds of them with nothing to do.
+constexpr int kSigPages = 12;
+constexpr int kSigGroups = 8192;
 
 // Kernel entry points of layout n (k_attn_l<n>.hip): which = 0 attn_decode,
 // 1 attn_significance, 2 attn_pair; nullptr for an unknown gq (and for

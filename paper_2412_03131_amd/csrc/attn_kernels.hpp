@@ -1687,9 +1687,10 @@ __global__ __launch_bounds__(kPairWaves * kWave, 1) void attn_pair(AttnArgs a)
 
 // ---------------------------------------------------------------------------
 // attn_significance: the significance update of one decode step (Sec. 4).  The
-// tokens are independent once the lse is known, so a table's pages are cut into
-// runs of kSigPages, one workgroup per (table, run); each of its four waves takes
-// every fourth page of the run (workgroups past a table's last page exit).  A page's
+// tokens are independent once the lse is known, so a table's pages are dealt in turn
+// to the waves of its workgroups, of which as many as give every wave three
+// pages work (the grid knows only how long a table can be); the others
+// exit.  A page's
 // key codes, key metadata, scores and positions are loaded; the logits of the
 // table's query heads come out of the key phase of do_page (lane = (group, token),
 // a transposed row sum), p = exp2(logit - lse) with the attention call's lse, the
@@ -1773,8 +1774,13 @@ __global__ __launch_bounds__(kSigWaves * kWave) void attn_significance(SigArgs a
 {
     using LY = Lay<LI>;
     constexpr int NS = (GQ + 3) / 4;
-    const int runs = (a.p_max + kSigPages - 1) / kSigPages;
-    const int t = blockIdx.x / runs, run = blockIdx.x - t * runs;
+    // Share-major, so the working workgroups come first and fall on all XCDs alike
+    // (workgroups go round-robin over the eight; table-major, six working of sixteen
+    // workgroups per table left two XCDs idle: 51 instead of 24 us), each share's
+    // tables turned by one, so that a long table's workgroups do too (76 instead
+    // of 64 us on tables that differ by a factor of ten).
+    const int T = a.B * a.Hkv;
+    const int share = blockIdx.x / T, t = (blockIdx.x - share * T + share) % T;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int grp = lane >> 4;
@@ -1784,8 +1790,9 @@ __global__ __launch_bounds__(kSigWaves * kWave) void attn_significance(SigArgs a
     const int len_hi = lenp[0], len_lo = lenp[1];
     const int N = a.seq_len[b];
     const int ph = (len_hi + LY::hi.T - 1) / LY::hi.T, np = ph + (len_lo + LY::lo.T - 1) / LY::lo.T;
-    const int p_end = np < (run + 1) * kSigPages ? np : (run + 1) * kSigPages;
-    if (run * kSigPages >= np) return;
+    const int want = (np + kSigPages - 1) / kSigPages;
+    const int nw = (want < a.shares ? want : a.shares) * kSigWaves, wv = share * kSigWaves + wave;
+    if (wv >= nw) return;
     // q pairs as in run_segment: lane k of a row holds its group's pair k
     // (dims d, d+4), pair 0 whole in every lane, the group's sum
     const int qm = (lane & 15) >> 2, qa = lane & 3;
@@ -1810,7 +1817,7 @@ __global__ __launch_bounds__(kSigWaves * kWave) void attn_significance(SigArgs a
         lse2[s] = hs < GQ ? a.lse[(long long)b * a.Hq + h * GQ + hs] * 1.4426950408889634f : 0.f;
     }
     const int32_t* trow = a.page_table + (long long)t * P;
-    for (int p = run * kSigPages + wave; p < p_end; p += kSigWaves) {
+    for (int p = wv; p < np; p += nw) {
         const int id = __builtin_amdgcn_readfirstlane(p < ph ? trow[p] : trow[P - 1 - (p - ph)]);
         if ((unsigned long long)(unsigned)id >= (unsigned long long)a.num_pages) continue;  // never outside the pool
         uint8_t* pg = a.pool + (long long)id * LY::page_bytes;

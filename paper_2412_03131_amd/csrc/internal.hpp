@@ -163,6 +163,7 @@ struct SigArgs {
     float scale_log2;
     const float* lse;   // [B][Hq] natural log, from the attention call
     int layout;         // index into kLayoutFmts
+    int shares;         // workgroups per table
 };
 hipError_t launch_significance(const SigArgs& a, hipStream_t st);
 // The mode an attention call with `splits` runs in on the current device:

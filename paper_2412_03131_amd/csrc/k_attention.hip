@@ -103,16 +103,21 @@ hipError_t launch_attention(AttnArgs a, hipStream_t st)
 }
 
 
-hipError_t launch_significance(const SigArgs& a, hipStream_t st)
+hipError_t launch_significance(const SigArgs& args, hipStream_t st)
 {
+    SigArgs a = args;
     const int gq = a.Hq / a.Hkv;
     const void* kern = attn_kernel_ptr(a.layout, gq, 1);
     if (!kern) return hipErrorInvalidValue;
     const long long T = (long long)a.B * a.Hkv;
-    const long long grid = T * ((a.p_max + kSigPages - 1) / kSigPages);
-    if (T < 1 || grid > INT32_MAX) return hipErrorInvalidValue;
-    void* args[] = {const_cast<SigArgs*>(&a)};
-    return hipLaunchKernel(kern, dim3((unsigned)grid), dim3(kSigWaves * kWave), args, 0, st);
+    if (T < 1) return hipErrorInvalidValue;
+    const long long most = (a.p_max + kSigPages - 1) / kSigPages;
+    const long long shares = (kSigGroups + T - 1) / T;
+    a.shares = (int)(shares < most ? shares : most);
+    const long long grid = T * a.shares;
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    void* kargs[] = {&a};
+    return hipLaunchKernel(kern, dim3((unsigned)grid), dim3(kSigWaves * kWave), kargs, 0, st);
 }
 
 }  // namespace dkv

@@ -1,0 +1,40 @@
+"""The significance update's deal of pages to workgroups: tables with fewer pages than the
+grid gives them workgroups, with more than a workgroup's twelve (several workgroups), and
+so many tables that each has one workgroup for a long table's pages."""
+import numpy as np
+import pytest
+from test_gpu_significance import _compare, _step
+
+from gpu_util import dev_cache_from_oracle, layouts
+from oracle import oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hkv,gq,lens", [
+    (3, 2, 4, (191, 193, 400)),   # 12, 13 and 25 pages
+    (7, 1, 5, (0, 1, 16, 17, 180, 200, 900)),
+    (1025, 8, 1, (700, 3)),       # 8200 tables: one workgroup each
+])
+def test_pages_dealt_to_workgroups(B, Hkv, gq, lens):
+    rng = np.random.default_rng(B)
+    new_len = np.zeros(B, np.int32)
+    new_len[:len(lens)] = lens
+    rows = int(new_len.sum())
+    k = (rng.standard_normal((rows, Hkv, 128)) * 2).astype(np.float16).view(np.uint16)
+    v = rng.standard_normal((rows, Hkv, 128)).astype(np.float16).view(np.uint16)
+    score = (rng.random((rows, Hkv)) * 0.01).astype(np.float32)
+    quota = np.zeros((B, Hkv, 2), np.int32)
+    quota[:, :, 0] = new_len[:, None]
+    quota[:, ::2, 0] //= 2
+    quota[:, ::2, 1] = new_len[:, None] - quota[:, ::2, 0]
+    Lo, Ld = layouts(max_seq_len=1024)
+    pages = int((-(-quota // 16)).sum()) + 64
+    oc = orc.Cache(Lo, pages, B, Hkv, ring=rng.permutation(pages))
+    orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+    assert oc.status[0] == 0
+    dc = dev_cache_from_oracle(Ld, oc)
+    q = rng.standard_normal((B, gq * Hkv, 128)).astype(np.float16).view(np.uint16)
+    print("case: significance pages dealt, B=%d" % B, flush=True)
+    _step(dc, oc, q)
+    assert _compare(dc, oc, "B=%d" % B) == rows * Hkv
