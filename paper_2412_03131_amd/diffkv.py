@@ -6,6 +6,7 @@ Loading fails loudly when the library has not been built.
 """
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -64,7 +65,7 @@ def lib():
         L = C.CDLL(LIB_PATH)
         vp, i32, i64, f32, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_size_t
         PL = C.POINTER(Layout)
-        PC = C.POINTER(CacheStruct)
+        PC = vp  # a CacheStruct by reference, or its packed bytes (_cache_bytes)
         L.diffkv_layout_init.argtypes = [PL, i32, i32, vp, vp, vp, i32]
         L.diffkv_workspace_size.argtypes = [i32, PL, i32, i32, i32, i64, i32, C.POINTER(sz)]
         L.diffkv_quantize_append.argtypes = [PL, PC, i64, i32, vp, vp, vp, vp, vp, f32, f32, i32,
@@ -95,13 +96,13 @@ def _check(code, what):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is None:  # the current device's current stream, as an address
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def layout(head_dim=128, group=32, k_bits=(8, 4), v_bits=(4, 2), tokens_per_page=(16, 32),
@@ -122,12 +123,30 @@ def workspace_size(op, L, num_seqs, num_q_heads=0, num_kv_heads=1, total_new=0, 
     return n.value
 
 
-def _ws(nbytes, device, ws):
-    if ws is not None:
-        if ws.numel() * ws.element_size() < nbytes:
-            raise ValueError("workspace too small: need %d bytes" % nbytes)
-        return ws
+# The calls below cost the host what a short kernel costs the device, so what they
+# marshal is kept to the call's own arguments: the cache's addresses packed into
+# bytes, the stream's address, plain integers, and no size query for a workspace
+# that the caller brings (the library checks its size).
+_CACHE = struct.Struct("PqPPPPPPPii")
+assert _CACHE.size == C.sizeof(CacheStruct)
+
+
+def _cache_bytes(c):
+    return _CACHE.pack(c.pool.data_ptr(), c.num_pages, c.page_table.data_ptr(), c.pages.data_ptr(),
+                       c.len.data_ptr(), c.seq_len.data_ptr(), c.ring.data_ptr(), c.ring_ptr.data_ptr(),
+                       c.status.data_ptr(), c.num_seqs, c.num_kv_heads)
+
+
+def _new_ws(nbytes, device):
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+
+
+def _check_ws(code, what, *sizes):
+    """As _check; a workspace that is too small is a ValueError that says what is needed."""
+    if code == E_WORKSPACE:
+        raise ValueError("workspace too small: need %d bytes" % workspace_size(*sizes))
+    if code != OK:
+        raise DiffKVError(code, what)
 
 
 class Cache:
@@ -195,13 +214,13 @@ def quantize_append(cache, new_len, k, v, score, quota=None, alpha_h=0.0, alpha_
         nl = new_len.cpu()
         total_new = int(nl.sum()) if total_new is None else total_new
         max_new = int(nl.max()) if max_new is None else max_new
-    need = workspace_size(OP_APPEND, L, cache.num_seqs, 0, cache.num_kv_heads, total_new)
-    ws = _ws(need, cache.pool.device, ws)
-    st = cache.struct()
-    _check(lib().diffkv_quantize_append(
-        C.byref(L), C.byref(st), int(total_new), int(max_new), _ptr(new_len), _ptr(_bits16(k)),
+    sizes = (OP_APPEND, L, cache.num_seqs, 0, cache.num_kv_heads, total_new)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), cache.pool.device)
+    _check_ws(lib().diffkv_quantize_append(
+        C.byref(L), _cache_bytes(cache), int(total_new), int(max_new), _ptr(new_len), _ptr(_bits16(k)),
         _ptr(_bits16(v)), _ptr(score), _ptr(quota), float(alpha_h), float(alpha_l), int(window),
-        _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)), "diffkv_quantize_append")
+        ws.data_ptr(), ws.nbytes, _stream(stream)), "diffkv_quantize_append", *sizes)
     return ws
 
 
@@ -214,22 +233,20 @@ def decode_attention(cache, q, sm_scale, out=None, lse=None, num_splits=0, ws=No
         out = torch.empty((B, Hq, D), dtype=torch.float32, device=q.device)
     if lse is None and want_lse:
         lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    need = workspace_size(OP_ATTENTION, L, cache.num_seqs, Hq, cache.num_kv_heads, 0, num_splits)
-    ws = _ws(need, q.device, ws)
-    st = cache.struct()
-    _check(lib().diffkv_decode_attention(
-        C.byref(L), C.byref(st), Hq, _ptr(_bits16(q)), float(sm_scale), _ptr(out), _ptr(lse),
-        int(num_splits), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)),
-        "diffkv_decode_attention")
+    sizes = (OP_ATTENTION, L, cache.num_seqs, Hq, cache.num_kv_heads, 0, num_splits)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), q.device)
+    _check_ws(lib().diffkv_decode_attention(
+        C.byref(L), _cache_bytes(cache), Hq, _ptr(_bits16(q)), float(sm_scale), _ptr(out), _ptr(lse),
+        int(num_splits), ws.data_ptr(), ws.nbytes, _stream(stream)), "diffkv_decode_attention", *sizes)
     return out, lse
 
 
 def decode_attention_noalloc(cache, q, sm_scale, out, lse=None, num_splits=0, stream=None):
     """diffkv_decode_attention_noalloc: like decode_attention, outputs given by the
     caller, no workspace (the library's fixed per-device scratch)."""
-    st = cache.struct()
     _check(lib().diffkv_decode_attention_noalloc(
-        C.byref(cache.L), C.byref(st), q.shape[1], _ptr(_bits16(q)), float(sm_scale), _ptr(out),
+        C.byref(cache.L), _cache_bytes(cache), q.shape[1], _ptr(_bits16(q)), float(sm_scale), _ptr(out),
         _ptr(lse), int(num_splits), _stream(stream)), "diffkv_decode_attention_noalloc")
     return out, lse
 
@@ -238,8 +255,7 @@ def update_significance(cache, q, sm_scale, lse, stream=None):
     """diffkv_update_significance: every kept token's score becomes the running mean of
     its attention probability (max over the KV head's query heads); lse from
     decode_attention with the same q."""
-    st = cache.struct()
-    _check(lib().diffkv_update_significance(C.byref(cache.L), C.byref(st), q.shape[1], _ptr(_bits16(q)),
+    _check(lib().diffkv_update_significance(C.byref(cache.L), _cache_bytes(cache), q.shape[1], _ptr(_bits16(q)),
                                             float(sm_scale), _ptr(lse), _stream(stream)),
            "diffkv_update_significance")
 
@@ -255,12 +271,13 @@ def prompt_significance(L, new_len, q, k, sm_scale, lse=None, score=None, max_ne
         max_new = int(new_len.max().item()) if B else 0
     if score is None:
         score = torch.empty((rows, Hkv), dtype=torch.float32, device=q.device)
-    need = workspace_size(OP_PROMPT_SIGNIFICANCE, L, B, Hq, Hkv, rows)
-    ws = _ws(need, q.device, ws)
-    _check(lib().diffkv_prompt_significance(C.byref(L), B, rows, int(max_new), _ptr(new_len), Hq, Hkv,
-                                            _ptr(_bits16(q)), _ptr(_bits16(k)), float(sm_scale), _ptr(lse),
-                                            _ptr(score), _ptr(ws), ws.numel() * ws.element_size(),
-                                            _stream(stream)), "diffkv_prompt_significance")
+    sizes = (OP_PROMPT_SIGNIFICANCE, L, B, Hq, Hkv, rows)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), q.device)
+    _check_ws(lib().diffkv_prompt_significance(C.byref(L), B, rows, int(max_new), _ptr(new_len), Hq, Hkv,
+                                               _ptr(_bits16(q)), _ptr(_bits16(k)), float(sm_scale), _ptr(lse),
+                                               _ptr(score), ws.data_ptr(), ws.nbytes, _stream(stream)),
+              "diffkv_prompt_significance", *sizes)
     return score
 
 
@@ -268,12 +285,11 @@ def compact_free_list(cache, release, num_tables=None, ws=None, stream=None):
     """release uint8 [num_tables, p_max] (device)."""
     L = cache.L
     nt = cache.num_tables if num_tables is None else num_tables
-    need = workspace_size(OP_COMPACT, L, cache.num_seqs, 0, cache.num_kv_heads)
-    ws = _ws(need, cache.pool.device, ws)
-    st = cache.struct()
-    _check(lib().diffkv_compact_free_list(C.byref(L), C.byref(st), int(nt), _ptr(release),
-                                          _ptr(ws), ws.numel() * ws.element_size(),
-                                          _stream(stream)), "diffkv_compact_free_list")
+    sizes = (OP_COMPACT, L, cache.num_seqs, 0, cache.num_kv_heads)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), cache.pool.device)
+    _check_ws(lib().diffkv_compact_free_list(C.byref(L), _cache_bytes(cache), int(nt), _ptr(release), ws.data_ptr(), ws.nbytes,
+                       _stream(stream)), "diffkv_compact_free_list", *sizes)
     return ws
 
 
@@ -281,23 +297,21 @@ def alloc_pages(cache, demand, num_tables=None, ws=None, stream=None):
     """demand int32 [num_tables, 2] (device)."""
     L = cache.L
     nt = cache.num_tables if num_tables is None else num_tables
-    need = workspace_size(OP_ALLOC, L, cache.num_seqs, 0, cache.num_kv_heads)
-    ws = _ws(need, cache.pool.device, ws)
-    st = cache.struct()
-    _check(lib().diffkv_alloc_pages(C.byref(L), C.byref(st), int(nt), _ptr(demand), _ptr(ws),
-                                    ws.numel() * ws.element_size(), _stream(stream)),
-           "diffkv_alloc_pages")
+    sizes = (OP_ALLOC, L, cache.num_seqs, 0, cache.num_kv_heads)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), cache.pool.device)
+    _check_ws(lib().diffkv_alloc_pages(C.byref(L), _cache_bytes(cache), int(nt), _ptr(demand), ws.data_ptr(), ws.nbytes,
+                       _stream(stream)), "diffkv_alloc_pages", *sizes)
     return ws
 
 
 def generation_step(cache, alpha_h, alpha_l, recent_window, ws=None, stream=None):
     """One decode step's generation-phase policy for every table (Algorithm 1)."""
     L = cache.L
-    need = workspace_size(OP_GENERATION, L, cache.num_seqs, 0, cache.num_kv_heads)
-    ws = _ws(need, cache.pool.device, ws)
-    st = cache.struct()
-    _check(lib().diffkv_generation_step(C.byref(L), C.byref(st), float(alpha_h), float(alpha_l),
-                                        int(recent_window), _ptr(ws),
-                                        ws.numel() * ws.element_size(), _stream(stream)),
-           "diffkv_generation_step")
+    sizes = (OP_GENERATION, L, cache.num_seqs, 0, cache.num_kv_heads)
+    if ws is None:
+        ws = _new_ws(workspace_size(*sizes), cache.pool.device)
+    _check_ws(lib().diffkv_generation_step(C.byref(L), _cache_bytes(cache), float(alpha_h), float(alpha_l),
+                                           int(recent_window), ws.data_ptr(), ws.nbytes, _stream(stream)),
+              "diffkv_generation_step", *sizes)
     return ws
