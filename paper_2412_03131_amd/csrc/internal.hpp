@@ -50,6 +50,7 @@ struct AppendArgs : LayoutArgs {
     long long* tplan;    // [tables] exclusive prefix (new pages | jobs << 32), planned path
     int32_t* job_table;  // [job_cap] table of each page job, planned path
     int job_cap;
+    int cls_split;       // classify workgroups per table
 };
 
 // Above this many tables an append plans once in its own launch instead of in

@@ -20,6 +20,8 @@
 // compact_apply) follow the same planning/coordination split:
 // per-table work is fully parallel, one prefix sum gives every table a
 // disjoint ring region.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "quant.hpp"
 
@@ -38,13 +40,24 @@ __device__ __forceinline__ uint32_t score_key(float s)
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------------------------
-// append_classify: grid B * Hkv (table t = b * Hkv + h), block 512
+// append_classify: table t = b * Hkv + h, block 512.  One workgroup per table, or
+// (few tables with long prompts) cls_split of them, each classing a run of its
+// table's tiles of 4096 tokens: every one selects the cuts and counts the classes
+// of the tiles before its own again, which costs it a read of the scores, where
+// one workgroup after the other would rank them (two prompts of 32k tokens, 16
+// tables: 53 us in one workgroup per table).
+// Thread tid takes tokens tid, tid + 512, ... of a tile, so a wave's scores come
+// from neighbouring rows and its ranks from ballots.
 // ---------------------------------------------------------------------------
 constexpr int kClsThreads = 512;
 static_assert(kClsThreads >= 2 * kWave, "two waves scan the digit histograms");
 constexpr int kClsPer = 8;                       // tokens per thread in one tile
 static_assert(4 * kClsPer <= 32, "a thread keeps four flag bits per token of a tile in one 32-bit word");
 constexpr int kClsTile = kClsThreads * kClsPer;  // the first tile's scores stay in registers
+constexpr int kClsWaves = kClsThreads / kWave;
+static_assert(kClsPer * kClsWaves == kWave, "a wave scans a tile's counts");
+constexpr int kClsBusyGroups = 512;  // workgroups that keep the device busy (two per CU)
+static_assert(kClsTile < 65536, "16-bit counts");
 constexpr uint32_t kOffSat = 1u << 30;           // row offsets saturate here (above any total_new)
 
 // Sum over the wave of values <= kOffSat, saturating at kOffSat (result in lane 63).
@@ -71,20 +84,22 @@ struct Cuts {
 
 __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
 {
-    const int H = a.Hkv;
-    const int t = blockIdx.x;
+    const int H = a.Hkv, NT = a.B * H;
+    const int split = blockIdx.x / NT, t = blockIdx.x - split * NT;
     const int b = t / H, h = t - b * H;
     const int tid = threadIdx.x;
-    __shared__ long long s_scan[kClsThreads / kWave];
+    __shared__ long long s_cnt[2][kClsPer * kClsWaves];  // a tile's class counts by step and wave, in position order
+    __shared__ int s_before[4];                          // class counts of the tiles before this workgroup's
     __shared__ int s_hist[2][2][256];  // [buffer][cut][digit]
     __shared__ int s_sel[4];
     __shared__ uint32_t s_off;
 
-    if (t == 0 && tid == 0) {  // ring pointers before this call (the commit kernel moves head)
+    if (t == 0 && split == 0 && tid == 0) {  // ring pointers before this call (the commit kernel moves head)
         a.flags->head_old = a.ring_ptr[0];
         a.flags->tail_old = a.ring_ptr[1];
     }
     for (int i = tid; i < 512; i += kClsThreads) (&s_hist[0][0][0])[i] = 0;
+    if (tid < 4) s_before[tid] = 0;
     // row offset of this sequence: sum of new_len over lower sequences (wave 0).
     // Entries are clamped to [0, kOffSat] and the sum saturates: a call with an
     // entry outside [0, max_new] fails anyway (that table flags itself).
@@ -99,7 +114,7 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     }
     const int n = a.new_len[b];
     TState* ts = a.tstate + t;
-    if (tid == 0) {  // section lengths and pages before this call
+    if (split == 0 && tid == 0) {  // section lengths and pages before this call
         ts->lold[0] = a.len[2 * t];
         ts->lold[1] = a.len[2 * t + 1];
         ts->pold[0] = a.pages[2 * t];
@@ -116,13 +131,18 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     const bool bad = n < 0 || n > a.max_new || off_b + n > a.total_new ||
                      (b == a.B - 1 && off_b + n != a.total_new);
     if (bad) {
-        if (tid == 0) {  // the commit kernel turns n < 0 into DIFFKV_ST_BAD_INPUT
+        if (split == 0 && tid == 0) {  // the commit kernel turns n < 0 into DIFFKV_ST_BAD_INPUT
             ts->cnt[0] = ts->cnt[1] = 0;
             ts->n = -1;
         }
         return;
     }
-    if (h == 0 && tid == 0) {
+    // this workgroup's tiles [c0, c1) of the table's
+    const int tiles = n > kClsTile ? (n + kClsTile - 1) / kClsTile : 1;
+    const int per = (tiles + a.cls_split - 1) / a.cls_split;
+    const int c0 = split * per, c1 = c0 + per < tiles ? c0 + per : tiles;
+    if (c0 >= tiles) return;
+    if (h == 0 && split == 0 && tid == 0) {
         a.sold[b] = a.seq_len[b];
         a.row_off[b] = (int)off_b;
     }
@@ -131,15 +151,16 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     const float* sc = a.score + off_b * H + h;
     int32_t* ord = a.ord + off_b * H + (long long)h * n;
 
-    // first tile: thread tid holds tokens tid*e .. tid*e + e - 1
-    const int n0 = n < kClsTile ? n : kClsTile;
-    const int e = (n0 + kClsThreads - 1) / kClsThreads;
-    float sr[kClsPer];
+    // scores of step i .. of a tile from `base` on, kClsPer steps' loads together
+    auto load_scores = [&](int base, float (&v)[kClsPer]) {
 #pragma unroll
-    for (int i = 0; i < kClsPer; ++i) {
-        const int j = tid * e + i;
-        sr[i] = (i < e && j < avail) ? sc[(long long)j * H] : 0.f;
-    }
+        for (int i = 0; i < kClsPer; ++i) {
+            const int j = base + i * kClsThreads + tid;
+            v[i] = j < avail ? sc[(long long)j * H] : 0.f;
+        }
+    };
+    float sr[kClsPer];  // the first tile's stay in registers
+    load_scores(0, sr);
 
     Cuts c = {{0, 0}, {0, 0}, {0, 0}};
     float thr_h = 0.f, thr_l = 0.f;
@@ -161,22 +182,26 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
             for (int pass = 0; pass < 4; ++pass) {
                 const int shift = 24 - 8 * pass;
                 int* hist = &s_hist[pass & 1][0][0];
+                auto digits = [&](int base, const uint32_t (&k8)[kClsPer]) {
 #pragma unroll
-                for (int i = 0; i < kClsPer; ++i) {
-                    if (i < e && tid * e + i < avail) {
-                        const uint32_t key = kr[i];
-                        const uint32_t dig = (key >> shift) & 255u;
+                    for (int i = 0; i < kClsPer; ++i) {
+                        if (base + i * kClsThreads + tid < avail) {
+                            const uint32_t key = k8[i];
+                            const uint32_t dig = (key >> shift) & 255u;
 #pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2)
-                            if (kk[s2] > 0 && (key & mask) == prefix[s2]) atomicAdd(&hist[s2 * 256 + dig], 1);
+                            for (int s2 = 0; s2 < 2; ++s2)
+                                if (kk[s2] > 0 && (key & mask) == prefix[s2]) atomicAdd(&hist[s2 * 256 + dig], 1);
+                        }
                     }
-                }
-                for (int j = kClsTile + tid; j < avail; j += kClsThreads) {  // beyond the first tile
-                    const uint32_t key = score_key(sc[(long long)j * H]);
-                    const uint32_t dig = (key >> shift) & 255u;
+                };
+                digits(0, kr);
+                for (int base = kClsTile; base < avail; base += kClsTile) {  // beyond the first tile
+                    float v[kClsPer];
+                    load_scores(base, v);
+                    uint32_t k8[kClsPer];
 #pragma unroll
-                    for (int s2 = 0; s2 < 2; ++s2)
-                        if (kk[s2] > 0 && (key & mask) == prefix[s2]) atomicAdd(&hist[s2 * 256 + dig], 1);
+                    for (int i = 0; i < kClsPer; ++i) k8[i] = score_key(v[i]);
+                    digits(base, k8);
                 }
                 for (int i = tid; i < 512; i += kClsThreads) (&s_hist[(pass + 1) & 1][0][0])[i] = 0;  // the next digit's buffer
                 __syncthreads();
@@ -230,75 +255,93 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     }
 
     // ---- classes and in-section ranks, in position order ------------------
-    // One block scan per tile of four counters (16 bits each): above cut 0,
-    // tied at cut 0, above cut 1, tied at cut 1.  The high set is the cut-0
-    // set; the low set is the cut-1 set minus it (cut 1's set contains cut 0's),
-    // so a token's rank in either follows from the four prefix counts.
-    int c_a0 = 0, c_e0 = 0, c_a1 = 0, c_e1 = 0;
-    for (int base = 0; base < n; base += kClsTile) {
-        const int tn = n - base < kClsTile ? n - base : kClsTile;
-        const int et = (tn + kClsThreads - 1) / kClsThreads;
-        uint32_t fl = 0;  // 4 flag bits per token
-        long long cnt = 0;
+    // Flags of a token: above cut 0, tied at cut 0, above cut 1, tied at cut 1.
+    // The high set is the cut-0 set; the low set is the cut-1 set minus it (cut
+    // 1's set contains cut 0's), so a token's rank in either follows from the
+    // four counts before it.
+    auto flags_of = [&](int j, float s) -> uint32_t {
+        if (j >= n) return 0u;
+        if (j >= avail) return 5u;  // recent window: always high
+        if (quota) {
+            const uint32_t key = score_key(s);
+            const uint32_t f0 = c.mode[0] == 1 ? 1u : (c.mode[0] == 2 ? (uint32_t)(key > c.K[0]) | ((uint32_t)(key == c.K[0]) << 1) : 0u);
+            const uint32_t f1 = c.mode[1] == 1 ? 1u : (c.mode[1] == 2 ? (uint32_t)(key > c.K[1]) | ((uint32_t)(key == c.K[1]) << 1) : 0u);
+            return f0 | (f1 << 2);
+        }
+        const uint32_t a0 = s >= thr_h, a1 = a0 | (uint32_t)(s >= thr_l);
+        return a0 | (a1 << 2);
+    };
+    const int wave = wave_index(), lane = lane_id();
+    const uint64_t below = (1ull << lane) - 1ull;
+    int c_f[4] = {0, 0, 0, 0};  // counts before the tile
+    if (c0 > 0) {
+        int mine[4] = {0, 0, 0, 0};  // (uniform) this wave's
+        for (int base = 0; base < c0 * kClsTile; base += kClsTile) {
+            float v[kClsPer];
+            load_scores(base, v);
 #pragma unroll
-        for (int i = 0; i < kClsPer; ++i) {
-            const int j = base + tid * et + i;
-            if (i < et && j < n) {
-                bool a0, e0, a1, e1;
-                if (j >= avail) {  // recent window: always high
-                    a0 = a1 = true;
-                    e0 = e1 = false;
-                } else {
-                    const float s = base == 0 ? sr[i] : sc[(long long)j * H];
-                    if (quota) {
-                        const uint32_t key = score_key(s);
-                        a0 = c.mode[0] == 1 || (c.mode[0] == 2 && key > c.K[0]);
-                        e0 = c.mode[0] == 2 && key == c.K[0];
-                        a1 = c.mode[1] == 1 || (c.mode[1] == 2 && key > c.K[1]);
-                        e1 = c.mode[1] == 2 && key == c.K[1];
-                    } else {
-                        a0 = s >= thr_h;
-                        a1 = a0 || s >= thr_l;
-                        e0 = e1 = false;
-                    }
-                }
-                fl |= ((uint32_t)a0 | ((uint32_t)e0 << 1) | ((uint32_t)a1 << 2) | ((uint32_t)e1 << 3)) << (4 * i);
-                cnt += (long long)a0 | ((long long)e0 << 16) | ((long long)a1 << 32) | ((long long)e1 << 48);
+            for (int i = 0; i < kClsPer; ++i) {
+                const uint32_t f = flags_of(base + i * kClsThreads + tid, v[i]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) mine[q] += __popcll(__builtin_amdgcn_ballot_w64(f >> q & 1u));
             }
         }
-        long long tot;
-        const long long ex = block_excl_scan<long long>(cnt, s_scan, &tot);
-        int r_a0 = c_a0 + (int)(ex & 0xffff), r_e0 = c_e0 + (int)((ex >> 16) & 0xffff);
-        int r_a1 = c_a1 + (int)((ex >> 32) & 0xffff), r_e1 = c_e1 + (int)((ex >> 48) & 0xffff);
+        if (lane < 4) atomicAdd(&s_before[lane], lane == 0 ? mine[0] : (lane == 1 ? mine[1] : (lane == 2 ? mine[2] : mine[3])));
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kClsPer; ++i) {
-            const int j = base + tid * et + i;
-            if (i < et && j < n) {
-                const uint32_t f = fl >> (4 * i);
-                const bool a0 = f & 1, e0 = f & 2, a1 = f & 4, e1 = f & 8;
-                const int rh = r_a0 + min(r_e0, c.need[0]);  // high tokens before this one
-                const int rt = r_a1 + min(r_e1, c.need[1]);  // high + low tokens before it
-                // (the ranks stay inside the table's n slots; the bounds tests only guard memory)
-                if (a0 || (e0 && r_e0 < c.need[0])) {
-                    if (rh < n) ord[rh] = j;
-                } else if (a1 || (e1 && r_e1 < c.need[1])) {
-                    if ((unsigned)(rt - rh) < (unsigned)n) ord[n - 1 - (rt - rh)] = j;
-                }
-                r_a0 += a0;
-                r_e0 += e0;
-                r_a1 += a1;
-                r_e1 += e1;
-            }
-        }
-        c_a0 += (int)(tot & 0xffff);
-        c_e0 += (int)((tot >> 16) & 0xffff);
-        c_a1 += (int)((tot >> 32) & 0xffff);
-        c_e1 += (int)((tot >> 48) & 0xffff);
+        for (int q = 0; q < 4; ++q) c_f[q] = s_before[q];
     }
-    if (tid == 0) {
-        const int hi = c_a0 + min(c_e0, c.need[0]);
+    for (int ct = c0; ct < c1; ++ct) {
+        const int base = ct * kClsTile;
+        float v[kClsPer];
+        if (ct > 0) {
+            load_scores(base, v);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kClsPer; ++i) v[i] = sr[i];
+        }
+        // per step and wave the four counts, 16 bits each (a tile has 4096 tokens)
+        uint32_t fl = 0;  // four flag bits per token
+        long long* cnt = s_cnt[ct & 1];
+#pragma unroll
+        for (int i = 0; i < kClsPer; ++i) {
+            const uint32_t f = flags_of(base + i * kClsThreads + tid, v[i]);
+            fl |= f << (4 * i);
+            long long p = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p |= (long long)__popcll(__builtin_amdgcn_ballot_w64(f >> q & 1u)) << (16 * q);
+            if (lane == 0) cnt[i * kClsWaves + wave] = p;
+        }
+        __syncthreads();  // (the other buffer is free again: every wave has passed its last barrier's reads)
+        const long long own = cnt[lane];
+        const long long incl = wave_incl_scan64(own), excl = incl - own;  // (no carry between the 16-bit fields)
+        const long long tot = read_lane<long long>(incl, kWave - 1);
+#pragma unroll
+        for (int i = 0; i < kClsPer; ++i) {
+            if (base + i * kClsThreads >= n) break;  // (uniform)
+            const uint32_t f = fl >> (4 * i);
+            const long long ex = read_lane<long long>(excl, i * kClsWaves + wave);
+            int r[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                r[q] = c_f[q] + (int)(ex >> (16 * q) & 0xffff) + __popcll(__builtin_amdgcn_ballot_w64(f >> q & 1u) & below);
+            const int j = base + i * kClsThreads + tid;
+            const int rh = r[0] + min(r[1], c.need[0]);  // high tokens before this one
+            const int rt = r[2] + min(r[3], c.need[1]);  // high + low tokens before it
+            // (the ranks stay inside the table's n slots; the bounds tests only guard memory)
+            if ((f & 1u) || ((f & 2u) && r[1] < c.need[0])) {
+                if (rh < n) ord[rh] = j;
+            } else if ((f & 4u) || ((f & 8u) && r[3] < c.need[1])) {
+                if ((unsigned)(rt - rh) < (unsigned)n) ord[n - 1 - (rt - rh)] = j;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c_f[q] += (int)(tot >> (16 * q) & 0xffff);
+    }
+    if (tid == 0 && c1 == tiles) {
+        const int hi = c_f[0] + min(c_f[1], c.need[0]);
         ts->cnt[0] = hi;
-        ts->cnt[1] = c_a1 + min(c_e1, c.need[1]) - hi;
+        ts->cnt[1] = c_f[2] + min(c_f[3], c.need[1]) - hi;
         ts->n = n;
     }
 }
@@ -1088,6 +1131,21 @@ constexpr int kCountWaves = 4;       // waves of a compact_count workgroup
 constexpr int kCompactPlanIlp = 16;  // values a lane loads at once
 constexpr int kMaxGroups = kWave * kCompactPlanIlp;
 
+// A wave's walk over a row of P slots, the lane taking s0, s0 + 64, ...: f(s0, n)
+// takes n of them with their loads in flight together (past the row's end, its
+// last slot's again), one on rows that a wave covers once, else four or eight
+// (rows of 2113 slots: count 12.6 -> 6.2 us, apply 20 -> 11 us).
+template <typename F>
+__device__ __forceinline__ void row_steps(int P, int lane, F&& f)
+{
+    auto walk = [&](auto n) {
+        for (int s0 = lane; s0 < P; s0 += decltype(n)::value * kWave) f(s0, n);
+    };
+    if (P <= kWave) walk(std::integral_constant<int, 1>{});
+    else if (P <= 4 * kWave) walk(std::integral_constant<int, 4>{});
+    else walk(std::integral_constant<int, 8>{});
+}
+
 // ONE: one table per wave (group_tables == kCountWaves, up to kMaxGroups * kCountWaves tables)
 template <bool ONE>
 __global__ __launch_bounds__(kCountWaves * kWave) void compact_count(CompactArgs a)
@@ -1106,7 +1164,17 @@ __global__ __launch_bounds__(kCountWaves * kWave) void compact_count(CompactArgs
         pl = pl < 0 ? 0 : (pl > P - ph ? P - ph : pl);
         const uint8_t* rel = a.release + (long long)t * P;
         int c = 0;
-        for (int s = lane; s < P; s += kWave) c += (rel[s] != 0 && slot_live(s, ph, pl, P));
+        row_steps(P, lane, [&](int s0, auto ilp) {
+            constexpr int N = decltype(ilp)::value;
+            uint8_t r[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) r[i] = rel[min(s0 + i * kWave, P - 1)];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int s = s0 + i * kWave;
+                c += (s < P && r[i] != 0 && slot_live(s, ph, pl, P));
+            }
+        });
         c = wave_isum_w<kWave>(c);
         if (lane == 0) a.count[t] = c;
         gsum += c;
@@ -1173,7 +1241,20 @@ __global__ __launch_bounds__(kWave) void compact_apply(CompactArgs a)
     int32_t* s_new = s_row + P;
     // the whole row, without waiting for the page counts: every load of the
     // wave is then in flight at once (slots outside the sections are not read)
-    for (int s = lane; s < P; s += kWave) s_row[s] = row[s] | (rel[s] != 0 ? (int32_t)0x80000000 : 0);
+    row_steps(P, lane, [&](int s0, auto ilp) {
+        constexpr int N = decltype(ilp)::value;
+        int32_t id[N];
+        uint8_t r[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int s = min(s0 + i * kWave, P - 1);
+            id[i] = row[s];
+            r[i] = rel[s];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (s0 + i * kWave < P) s_row[s0 + i * kWave] = id[i] | (r[i] != 0 ? (int32_t)0x80000000 : 0);
+    });
     tot = wave_isum_w<kWave>(tot);
     const int my_off = wave_isum_w<kWave>(before);
     if (t == 0 && lane == 0) a.ring_ptr[1] = tail_old + tot;
@@ -1245,10 +1326,16 @@ __global__ __launch_bounds__(kWave) void compact_apply(CompactArgs a)
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_append(const AppendArgs& a, int grid_quant, hipStream_t st)
+hipError_t launch_append(const AppendArgs& args, int grid_quant, hipStream_t st)
 {
+    AppendArgs a = args;
     if (append_one_call(a)) return launch1(append_one, (unsigned)(a.Hkv * a.B), kCommitThreads, st, a);
-    hipError_t e = launch1(append_classify, (unsigned)(a.Hkv * a.B), kClsThreads, st, a);
+    // a table's tiles go to several workgroups while there are fewer tables than CUs
+    const int tables = a.Hkv * a.B, tiles = (int)(((long long)a.max_new + kClsTile - 1) / kClsTile);
+    const int room = kClsBusyGroups / tables;
+    a.cls_split = tiles < room ? tiles : room;
+    if (a.cls_split < 1) a.cls_split = 1;
+    hipError_t e = launch1(append_classify, (unsigned)(tables * a.cls_split), kClsThreads, st, a);
     if (e != hipSuccess) return e;
     if (append_planned(a.B, a.Hkv)) {
         e = launch1(append_plan, 1, kPlanThreads, st, a);
