@@ -844,6 +844,8 @@ struct AttnShared {
     long long u_first;
     int rk_t[2];       // tables of the ranks searched (longest-first ranking)
     int rk_len[2][2];  // and their section lengths
+    int rk_bin[2], rk_in[2];  // their bins, and their places in them
+    int rk_sum[2][NW];        // the waves' sums
     int last;          // this workgroup is the last of a split table's shares
     unsigned long long tag;  // this call's tag (arrival words)
     long long units;         // balanced mode: the unit total of all tables
@@ -1283,21 +1285,24 @@ __device__ __forceinline__ void run_segment(const AttnArgs& a, AttnShared<GQ, NW
 // dispatched in index order and two share a CU for the whole launch, so
 // taking the tables longest first spreads the long ones over the CUs and
 // starts them first (longest-processing-time-first order).  Every workgroup
-// derives the same order from the section lengths; wave 0 does it alone
-// (wave-level scans, no workgroup barrier until the result).  Beyond kRankPer
-// tables per lane the order is the identity.  ti[k] gets the table's pages and
-// units, from the lengths the ranking wave already holds.
+// derives the same order from the section lengths with all its threads: each puts
+// its tables into the bins and adds up one or two bins, then counts its tables of
+// the ranks' bins (one wave alone, sixteen tables and sixteen bins per lane, took
+// 4.4 us of a 39 us call).  Above kRankTables tables the order is the identity.
+// ti[k] gets the table's pages and units, from the lengths its thread holds.
 constexpr int kKeep = 8;     // tables per thread whose units stay in registers (balanced mode)
-constexpr int kRankPer = 16;  // tables per lane of the ranking wave
+constexpr int kRankTables = 1024;  // most tables that are ranked
 
 template <int GQ, int LI, int NW, int NR>
 __device__ __forceinline__ void rank_tables(const AttnArgs& a, AttnShared<GQ, NW>& sh, CoefLds<GQ, NW>* coef, int T,
                                             const int (&rank)[NR], int (&tab)[NR], TableInfo (&ti)[NR])
 {
     static_assert(NR <= 2, "two ranks at most");
-    constexpr int kBins = 1024;
-    const int per = (T + kWave - 1) / kWave;
-    if (per > kRankPer) {
+    constexpr int kBins = 1024, NT = NW * kWave;
+    constexpr int kPer = (kRankTables + NT - 1) / NT;                   // tables per thread
+    constexpr int kBinPer = NT >= kBins ? 1 : 2;                        // bins per thread
+    static_assert(kBinPer * NT >= kBins, "every bin has a thread");
+    if (T > kRankTables) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             tab[k] = rank[k];
@@ -1306,87 +1311,86 @@ __device__ __forceinline__ void rank_tables(const AttnArgs& a, AttnShared<GQ, NW
         return;
     }
     static_assert(sizeof(CoefLds<GQ, NW>) >= kBins * sizeof(int), "histogram lives in the weight LDS");
-    if (threadIdx.x < kWave) {
-        int* hist = reinterpret_cast<int*>(coef);  // free until the page loop
-        const int lane = threadIdx.x;
-        const int t0 = lane * per, t1 = t0 + per < T ? t0 + per : T;
-        int shift = 0;
-        while (((Units<LI>::lo * a.p_max + Units<LI>::seg_pair) >> shift) >= kBins) ++shift;
-        int lh[kRankPer], ll[kRankPer], bin[kRankPer];
+    int* hist = reinterpret_cast<int*>(coef);  // free until the page loop
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int per = (T + NT - 1) / NT;  // a thread's tables follow each other: (thread, i) is the index order
+    const int t0 = tid * per;
+    int lh[kPer], ll[kPer], bin[kPer];
 #pragma unroll
-        for (int i = 0; i < kRankPer; ++i) {
-            const int tc = t0 + i < T ? t0 + i : T - 1;
-            lh[i] = i < per ? a.len[2 * tc] : 0;
-            ll[i] = i < per ? a.len[2 * tc + 1] : 0;
+    for (int i = 0; i < kPer; ++i) {
+        const int tc = t0 + i < T ? t0 + i : T - 1;
+        lh[i] = a.len[2 * tc];
+        ll[i] = a.len[2 * tc + 1];
+    }
+#pragma unroll
+    for (int q = 0; q < kBinPer; ++q)
+        if (tid * kBinPer + q < kBins) hist[tid * kBinPer + q] = 0;
+    int shift = 0;
+    while (((Units<LI>::lo * a.p_max + Units<LI>::seg_pair) >> shift) >= kBins) ++shift;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        bin[i] = -1;
+        if (i < per && t0 + i < T) {
+            const long long u = pair_units<LI>(table_info_of<LI>(a, lh[i], ll[i])) >> shift;
+            bin[i] = kBins - 1 - (int)(u < kBins - 1 ? u : kBins - 1);  // bin 0 holds the longest
+            atomicAdd(&hist[bin[i]], 1);
         }
-        static_assert(kBins == 16 * kWave, "sixteen bins per lane");
+    }
+    __syncthreads();
+    // exclusive prefix over the threads of one value (two per thread: NR of them)
+    auto wave_base = [&](const int* totals) {  // sum of totals[0 .. wave)
+        const int v = lane < NW ? totals[lane] : 0;
+        return __builtin_amdgcn_readlane(wave_incl_scan(v) - v, wave);
+    };
+    int c[kBinPer], s = 0;
 #pragma unroll
-        for (int q = 0; q < 16; q += 4) *reinterpret_cast<int4*>(hist + 16 * lane + q) = make_int4(0, 0, 0, 0);
-        wave_lds_sync();
+    for (int q = 0; q < kBinPer; ++q) {
+        c[q] = tid * kBinPer + q < kBins ? hist[tid * kBinPer + q] : 0;
+        s += c[q];
+    }
+    const int incl = wave_incl_scan(s);
+    if (lane == kWave - 1) sh.rk_sum[0][wave] = incl;
+    __syncthreads();
+    const int at0 = wave_base(sh.rk_sum[0]) + incl - s;
 #pragma unroll
-        for (int i = 0; i < kRankPer; ++i) {
-            bin[i] = -1;
-            if (t0 + i < t1) {
-                const long long u = pair_units<LI>(table_info_of<LI>(a, lh[i], ll[i])) >> shift;
-                bin[i] = kBins - 1 - (int)(u < kBins - 1 ? u : kBins - 1);  // bin 0 holds the longest
-                atomicAdd(&hist[bin[i]], 1);
+    for (int k = 0; k < NR; ++k) {
+        int at = at0;
+#pragma unroll
+        for (int q = 0; q < kBinPer; ++q) {
+            if (at <= rank[k] && rank[k] < at + c[q]) {  // one thread and bin (rank < T)
+                sh.rk_bin[k] = tid * kBinPer + q;
+                sh.rk_in[k] = rank[k] - at;
             }
+            at += c[q];
         }
-        wave_lds_sync();
-        int c16[16], s16 = 0;
+    }
+    __syncthreads();
+    // the rk_in-th table (by index) of each bin
+    int cnt[NR], inc[NR], rb[NR];
 #pragma unroll
-        for (int q = 0; q < 16; q += 4) {
-            const int4 v = *reinterpret_cast<const int4*>(hist + 16 * lane + q);
-            c16[q] = v.x; c16[q + 1] = v.y; c16[q + 2] = v.z; c16[q + 3] = v.w;
-        }
+    for (int k = 0; k < NR; ++k) {
+        rb[k] = sh.rk_bin[k];
+        cnt[k] = 0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s16 += c16[q];
-        const int incl = wave_incl_scan(s16);
+        for (int i = 0; i < kPer; ++i) cnt[k] += bin[i] == rb[k];
+        inc[k] = wave_incl_scan(cnt[k]);
+        if (lane == kWave - 1) sh.rk_sum[k][wave] = inc[k];
+    }
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < NR; ++k) {
-            const int j = rank[k];
-            int at = incl - s16, b = 0, r = 0;
-            bool found = false;
+    for (int k = 0; k < NR; ++k) {
+        int before = wave_base(sh.rk_sum[k]) + inc[k] - cnt[k];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                if (!found && at <= j && j < at + c16[q]) {
-                    found = true;
-                    b = 16 * lane + q;
-                    r = j - at;
+        for (int i = 0; i < kPer; ++i) {
+            if (bin[i] == rb[k]) {
+                if (before == sh.rk_in[k]) {
+                    sh.rk_t[k] = t0 + i;
+                    sh.rk_len[k][0] = lh[i];
+                    sh.rk_len[k][1] = ll[i];
                 }
-                at += c16[q];
-            }
-            const unsigned long long fm = __builtin_amdgcn_ballot_w64(found);  // exactly one lane (j < T)
-            const int src = fm ? __builtin_ctzll(fm) : 0;
-            b = __builtin_amdgcn_readlane(b, src);
-            r = __builtin_amdgcn_readlane(r, src);
-            // the r-th table (by index) of bin b
-            int cnt = 0;
-#pragma unroll
-            for (int i = 0; i < kRankPer; ++i) cnt += bin[i] == b;
-            int before = wave_incl_scan(cnt) - cnt, t = 0, th = 0, tl = 0;
-            found = false;
-#pragma unroll
-            for (int i = 0; i < kRankPer; ++i) {
-                if (bin[i] == b) {
-                    if (before == r) {
-                        found = true;
-                        t = t0 + i;
-                        th = lh[i];
-                        tl = ll[i];
-                    }
-                    ++before;
-                }
-            }
-            const unsigned long long fm2 = __builtin_amdgcn_ballot_w64(found);
-            const int src2 = fm2 ? __builtin_ctzll(fm2) : 0;
-            // read with every lane active
-            const int tr = __builtin_amdgcn_readlane(t, src2);
-            const int thr = __builtin_amdgcn_readlane(th, src2), tlr = __builtin_amdgcn_readlane(tl, src2);
-            if (lane == 0) {
-                sh.rk_t[k] = tr;
-                sh.rk_len[k][0] = thr;
-                sh.rk_len[k][1] = tlr;
+                ++before;
             }
         }
     }
