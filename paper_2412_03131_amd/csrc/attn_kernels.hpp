@@ -855,19 +855,6 @@ struct AttnShared {
     int own_k0, own_n;       // and the table's first workgroup and share count (0: the list is cut)
 };
 
-// Exclusive prefix sum of one 64-bit value per thread (0 <= x, sum below 2^52)
-// as two 32-bit counters, its low 20 bits and the rest: block_excl_scan adds
-// those through DPP, where a 64-bit sum would pass every step through LDS.
-__device__ __forceinline__ long long wg_excl_scan(long long x, long long* lds, long long* total)
-{
-    constexpr int kLow = 20;  // 1024 threads' low parts stay below 2^30
-    auto whole = [](long long p) { return ((p >> 32) << kLow) + (p & 0xffffffffLL); };
-    long long tot;
-    const long long e = block_excl_scan<long long>(((x >> kLow) << 32) | (x & ((1LL << kLow) - 1)), lds, &tot);
-    *total = whole(tot);
-    return whole(e);
-}
-
 __device__ __forceinline__ void write_empty(const AttnArgs& a, int t, int gq)
 {
     const int b = t / a.Hkv, h = t - b * a.Hkv;
@@ -1516,7 +1503,7 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
         if (u == 0 && t % W == k) write_empty_one(a, t, GQ);
     }
     long long total;
-    const long long before = wg_excl_scan(mine, sh.scan, &total);
+    const long long before = block_excl_scan_wide(mine, sh.scan, &total);
     if (threadIdx.x == 0) {
         sh.units = total;  // read back by the arrival (not kept in registers)
         sh.own_n = 0;

@@ -188,6 +188,21 @@ __device__ __forceinline__ TInt block_excl_scan(TInt x, TInt* lds, TInt* total, 
     return below + inc - x;
 }
 
+// The same for a true 64-bit value per thread (0 <= x, sum below 2^52), as two
+// 32-bit counters, its low 20 bits and the rest: those are added through DPP,
+// where a 64-bit sum would pass every step through LDS.
+__device__ __forceinline__ long long block_excl_scan_wide(long long x, long long* lds, long long* total, uint32_t bits = 0,
+                                                          uint32_t* lds_bits = nullptr, uint32_t* bits_out = nullptr)
+{
+    constexpr int kLow = 20;  // 1024 threads' low parts stay below 2^30
+    auto whole = [](long long p) { return ((p >> 32) << kLow) + (p & 0xffffffffLL); };
+    long long tot;
+    const long long e = block_excl_scan<long long>(((x >> kLow) << 32) | (x & ((1LL << kLow) - 1)), lds, &tot, bits,
+                                                   lds_bits, bits_out);
+    *total = whole(tot);
+    return whole(e);
+}
+
 // ---- arrival words --------------------------------------------------------
 // Workgroups of one launch that must find out which of them comes last count
 // themselves in a 64-bit word of the caller's workspace: a 44-bit call tag
@@ -265,33 +280,6 @@ __device__ __forceinline__ void arrive_claim_once(unsigned long long* w, unsigne
     if ((old >> kArriveCountBits) != tag)
         (void)__hip_atomic_compare_exchange_strong(w, &old, tag << kArriveCountBits, __ATOMIC_RELAXED,
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Block-wide sum of a true 64-bit value and OR of flag bits (all threads get
-// the result).  `lds` must hold blockDim.x/64 + 1 entries.
-__device__ __forceinline__ long long block_sum_or(long long x, uint32_t bits, long long* lds,
-                                                  uint32_t* bits_out)
-{
-    const int w = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        x += __shfl_xor(x, o, kWave);
-        bits |= (uint32_t)__shfl_xor((int)bits, o, kWave);
-    }
-    __shared__ uint32_t s_bits;
-    if (threadIdx.x == 0) s_bits = 0;
-    __syncthreads();
-    if (lane_id() == 0) {
-        lds[w] = x;
-        atomicOr(&s_bits, bits);
-    }
-    __syncthreads();
-    long long t = 0;
-    for (int i = 0; i < nw; ++i) t += lds[i];
-    *bits_out = s_bits;
-    __syncthreads();
-    return t;
 }
 
 // ---- fp16 helpers ----------------------------------------------------------

@@ -1045,58 +1045,90 @@ __global__ __launch_bounds__(kCommitThreads) void append_one(AppendArgs a)
 // ---------------------------------------------------------------------------
 // Allocation alone: alloc_plan (one workgroup) + alloc_write (wave per table)
 // ---------------------------------------------------------------------------
+// alloc_plan is a chain of one round of loads, one prefix sum and the stores, for as
+// many tables as a workgroup holds in registers (kAllocKeep per thread, tables in
+// thread order); it takes tables beyond those in further rounds, after a first
+// pass over all of them for the all-or-nothing verdict.  4096 tables: 7.6 us with
+// that pass and a 64-bit sum through shuffles for every size.
+constexpr int kAllocKeep = 8;
+
 __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
 {
     const int tid = threadIdx.x;
     const int NT = a.num_tables;
-    __shared__ long long s_scan[kPlanThreads / kWave + 1];
-    __shared__ long long s_head, s_tail;
-    if (tid == 0) {
-        s_head = a.ring_ptr[0];
-        s_tail = a.ring_ptr[1];
-    }
-    __syncthreads();
-    long long total = 0;
-    uint32_t flags = 0;
-    for (int t = tid; t < NT; t += kPlanThreads) {
-        int d0 = a.demand[2 * t], d1 = a.demand[2 * t + 1];
-        if (d0 < 0 || d1 < 0) flags |= DIFFKV_ST_BAD_INPUT;
-        total += (long long)(d0 > 0 ? d0 : 0) + (d1 > 0 ? d1 : 0);
-        if ((long long)a.pages[2 * t] + a.pages[2 * t + 1] + d0 + d1 > a.p_max)
-            flags |= DIFFKV_ST_TABLE_OVERFLOW;
-    }
-    uint32_t bits;
-    const long long total_all = block_sum_or(total, flags, s_scan, &bits);
-    if (total_all > s_tail - s_head) bits |= DIFFKV_ST_OUT_OF_PAGES;
-    if (bits) {
-        if (tid == 0) {
-            atomicOr(a.status, bits);
-            a.flags->ok = 0;
+    __shared__ long long s_scan[kPlanThreads / kWave];
+    __shared__ uint32_t s_bits[kPlanThreads / kWave];
+    const long long head = a.ring_ptr[0], tail = a.ring_ptr[1];
+    auto demand = [&](int t) { return make_int2(a.demand[2 * t], a.demand[2 * t + 1]); };
+    auto pages = [&](int t) { return make_int2(a.pages[2 * t], a.pages[2 * t + 1]); };
+    const bool kept = NT <= kAllocKeep * kPlanThreads;
+    const int per = kept ? (NT + kPlanThreads - 1) / kPlanThreads : kAllocKeep;
+    const int round = per * kPlanThreads;
+    auto need = [](int2 d) { return (long long)(d.x > 0 ? d.x : 0) + (d.y > 0 ? d.y : 0); };
+    auto check = [&](int2 d, int2 p) -> uint32_t {
+        return (d.x < 0 || d.y < 0 ? (uint32_t)DIFFKV_ST_BAD_INPUT : 0u) |
+               ((long long)p.x + p.y + d.x + d.y > a.p_max ? (uint32_t)DIFFKV_ST_TABLE_OVERFLOW : 0u);
+    };
+    int2 d[kAllocKeep], p[kAllocKeep];
+    auto load = [&](int t0) {  // tables t0 .. of this thread (the last again past the end)
+#pragma unroll
+        for (int i = 0; i < kAllocKeep; ++i) {
+            if (i >= per) break;  // (uniform)
+            const int t = min(t0 + i, NT - 1);
+            d[i] = demand(t);
+            p[i] = pages(t);
         }
-        return;
+    };
+    long long sum = 0, total;
+    uint32_t flags = 0, bits = 0;
+    if (kept) {
+        load(tid * per);
+    } else {
+        for (int t = tid; t < NT; t += kPlanThreads) {
+            const int2 dt = demand(t);
+            flags |= check(dt, pages(t));
+            sum += need(dt);
+        }
+        block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits);
+        if (total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
     }
     long long carry = 0;
-    for (int t0 = 0; t0 < NT; t0 += kPlanThreads) {
-        const int t = t0 + tid;
-        int d0 = 0, d1 = 0;
-        if (t < NT) {
-            d0 = a.demand[2 * t];
-            d1 = a.demand[2 * t + 1];
+    for (int r0 = 0; bits == 0 && r0 < NT; r0 += round) {
+        const int t0 = r0 + tid * per;
+        if (!kept) load(t0);
+        sum = 0;
+        flags = 0;
+#pragma unroll
+        for (int i = 0; i < kAllocKeep; ++i) {
+            if (i < per && t0 + i < NT) {
+                sum += need(d[i]);
+                flags |= check(d[i], p[i]);
+            }
         }
-        long long tr;
-        long long off = block_excl_scan<long long>(d0 + d1, s_scan, &tr) + carry;
-        carry += tr;
-        if (t < NT) {
-            int4 st = make_int4(a.pages[2 * t], a.pages[2 * t + 1], (int)off, d0);
-            a.tstate[t] = st;
-            a.pages[2 * t] = st.x + d0;
-            a.pages[2 * t + 1] = st.y + d1;
+        long long off = block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits) + carry;
+        if (kept && total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
+        if (bits) break;
+        carry += total;
+#pragma unroll
+        for (int i = 0; i < kAllocKeep; ++i) {
+            if (i < per && t0 + i < NT) {
+                const int t = t0 + i;
+                a.tstate[t] = make_int4(p[i].x, p[i].y, (int)off, d[i].x);
+                a.pages[2 * t] = p[i].x + d[i].x;
+                a.pages[2 * t + 1] = p[i].y + d[i].y;
+                off += d[i].x + d[i].y;
+            }
         }
     }
     if (tid == 0) {
-        a.flags->head_old = s_head;
-        a.flags->ok = 1;
-        a.ring_ptr[0] = s_head + carry;
+        if (bits) {
+            atomicOr(a.status, bits);
+            a.flags->ok = 0;
+        } else {
+            a.flags->head_old = head;
+            a.flags->ok = 1;
+            a.ring_ptr[0] = head + carry;
+        }
     }
 }
 
