@@ -1408,25 +1408,30 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
 // Balanced mode with little work per workgroup: each table gets shares of its own.
 // A call of eight 600-token tables has 136 pages for 512 workgroups; one equal cut
 // of the concatenated list gives a table 64 shares of a page or none, whose
-// arrivals and merge were the whole call (190 us; 10.5 now).  Shares that cross a
+// arrivals and merge were the whole call (190 us; 9.5 now).  Shares that cross a
 // table boundary also cost a second segment start and a second arrival.  So every
 // table is cut into ceil(p / quantum) equal ranges of its p page units, one
 // workgroup each, a table in one range having no merge, with quantum the largest of
 //   total / (W - T)     the ranges of T tables then fit the W workgroups;
 //   kOwnMin             a high page for every wave of the workgroup;
-//   kOwnRoot * sqrt(p)  a share's walk takes time in proportion to the quantum, the
-//                       merge in proportion to p / quantum, so the best quantum
-//                       grows with sqrt(p): 24, 49 and 112 units measured best on
-//                       tables of 244, 780 and 3122 (11.7, 13.4 and 19.0 us for one
-//                       sequence of 2500, 8000 and 32768 tokens at GQ 4; 144, 129
-//                       and 105 before).
+//   sqrt(p), kOwnMost   a share's walk takes time in proportion to the quantum, the
+//   at most             merge in proportion to p / quantum, so the quantum grows
+//                       with sqrt(p).  By time alone it would grow to 112 units on
+//                       a table of 3122; but the error of a long chain of v_dot2
+//                       sums grows with its length, and one table cut into all W
+//                       shares had short ones: at 2 sqrt(p) the error against 64
+//                       bits was up to 1.84 times that of the cut list, at most
+//                       20 units it is the same (1.00 to 1.12 times, 40 calls of
+//                       all layouts).  One sequence of 2500, 8000 and 32768 tokens
+//                       at GQ 4: 10.8, 15.7 and 24.7 us (11.4, 13.3 and 18.8 with
+//                       the longer chains; 150, 117 and 111 cut).
 // Rounding up to whole ranges makes the longest share total / (W - T) where the cut
 // list has total / W plus a segment's start, so the line lies where the two
 // differ by Units::seg (16 sequences of 2000 tokens, 128 tables: 16.5 against
 // 19.8 us; of 8192 tokens, over the line: 37 us cut).
 template <int LI, int NW>
 constexpr int kOwnMin = NW * Units<LI>::hi;
-constexpr float kOwnRoot = 2.0f;
+constexpr int kOwnMost = 20;
 
 template <int LI>
 __device__ __forceinline__ bool own_shares(long long total, int T, long long W)
@@ -1516,8 +1521,9 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
         auto shares_of = [&](long long un) {
             if (un <= 0) return 0;
             const int pu = (int)un - Units<LI>::seg;
-            const int root = (int)(kOwnRoot * __builtin_sqrtf((float)pu));
-            const int quantum = root > least ? root : least;
+            const int root = (int)__builtin_sqrtf((float)pu);
+            const int len = root < kOwnMost ? root : kOwnMost;
+            const int quantum = len > least ? len : least;
             return (pu + quantum - 1) / quantum;
         };
         int cnt = 0;

@@ -195,7 +195,7 @@ struct PromptArgs {
 // blocks than would keep the device busy, each block's queries are cut, down to
 // eight ways (the first block of one 4999-token prompt holds an eightieth of the
 // work of its 160 blocks, so the pass took as long as that one block: 867 us at 64
-// query heads, 296 us cut).  A sum over segments replaces the direct store.
+// query heads, 241 us cut).  A sum over segments replaces the direct store.
 constexpr int kPromptBusyBlocks = 2048;
 constexpr int kPromptMaxSegs = 8;
 inline int prompt_segs(long long B, long long Hkv, long long total_new)

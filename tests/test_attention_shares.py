@@ -30,7 +30,7 @@ def page_at_unit(x, ph, np_):
 def ranges_of(ph, pl, total, T, W, waves):
     need = -(-total // (W - T))
     pu = HI * ph + LO * pl
-    quantum = max(need, waves * HI, int(2.0 * math.sqrt(pu)))
+    quantum = max(need, waves * HI, min(20, int(math.sqrt(pu))))
     n = -(-pu // quantum)
     cut = [0] + [SEG + c * pu // n for c in range(1, n + 1)]
     return [(page_at_unit(cut[c], ph, ph + pl), page_at_unit(cut[c + 1], ph, ph + pl)) for c in range(n)]
