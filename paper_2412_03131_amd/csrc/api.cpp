@@ -431,7 +431,7 @@ diffkv_status diffkv_prompt_significance(const diffkv_layout* layout, int32_t nu
     a.B = num_seqs;
     a.Hq = num_q_heads;
     a.Hkv = num_kv_heads;
-    a.max_new = max_new;
+    a.max_new = max_new < total_new ? max_new : (int32_t)total_new;  // no sequence has more rows than there are
     a.total_new = total_new;
     a.new_len = new_len;
     a.q = q;

@@ -522,14 +522,14 @@ hipError_t launch_prompt_g(const PromptArgs& a, int cus, hipStream_t st)
     const long long pairs = (long long)a.B * a.Hkv;
     hipError_t e;
     if (!a.lse) {
-        const long long items = pairs * ((a.max_new + RowShape<G>::kPos - 1) / RowShape<G>::kPos) * RowShape<G>::kGroups;
-        if (items > 0x7fffffffLL) return hipErrorInvalidValue;
-        const long long grid = min(items, (long long)cus * RowShape<G>::kPerCu);
+        const long long blocks = pairs * ((a.max_new + RowShape<G>::kPos - 1) / RowShape<G>::kPos);
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        const long long grid = min(blocks * RowShape<G>::kGroups, (long long)cus * RowShape<G>::kPerCu);
         if ((e = launch1(ps_rows<G>, (unsigned)grid, RowShape<G>::kWaves * kWave, st, a)) != hipSuccess) return e;
     }
-    const long long items = pairs * ((a.max_new + kColKeys - 1) / kColKeys) * a.segs;
-    if (items > 0x7fffffffLL) return hipErrorInvalidValue;
-    e = launch1(ps_cols<G>, (unsigned)min(items, (long long)cus * 2), kPsThreads, st, a);
+    const long long blocks = pairs * ((a.max_new + kColKeys - 1) / kColKeys);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    e = launch1(ps_cols<G>, (unsigned)min(blocks * a.segs, (long long)cus * 2), kPsThreads, st, a);
     if (e != hipSuccess || a.segs == 1) return e;
     const long long rows = (long long)a.max_new * a.Hkv;
     const unsigned gx = (unsigned)min((rows + kPsThreads - 1) / kPsThreads, 64LL);
