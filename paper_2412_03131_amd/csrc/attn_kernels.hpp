@@ -1257,7 +1257,7 @@ __device__ __forceinline__ void run_segment(const AttnArgs& a, AttnShared<GQ, NW
 // attn_decode.
 //  splits = S >= 1: workgroup t*S + c takes range c of table t's pages, cut
 //    into min(S, pages) equal ranges (S = 1: no split).
-//  splits = -1: balanced shares.  Where own_shares() says so, each table is cut
+//  splits = -1: balanced shares.  Where they fit (kOwnUnits), each table is cut
 //    into ranges of its own.  Otherwise all tables' pages, in table order, form one
 //    list of U work units; workgroup k of W owns the pages whose first unit
 //    lies in [k*U/W, (k+1)*U/W).  Each workgroup finds its first table with a
@@ -1410,33 +1410,24 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
 // of the concatenated list gives a table 64 shares of a page or none, whose
 // arrivals and merge were the whole call (190 us; 9.5 now).  Shares that cross a
 // table boundary also cost a second segment start and a second arrival.  So every
-// table is cut into ceil(p / quantum) equal ranges of its p page units, one
-// workgroup each, a table in one range having no merge, with quantum the largest of
-//   total / (W - T)     the ranges of T tables then fit the W workgroups;
-//   kOwnMin             a high page for every wave of the workgroup;
-//   sqrt(p), kOwnMost   a share's walk takes time in proportion to the quantum, the
-//   at most             merge in proportion to p / quantum, so the quantum grows
-//                       with sqrt(p).  By time alone it would grow to 112 units on
-//                       a table of 3122; but the error of a long chain of v_dot2
-//                       sums grows with its length, and one table cut into all W
-//                       shares had short ones: at 2 sqrt(p) the error against 64
-//                       bits was up to 1.84 times that of the cut list, at most
-//                       20 units it is the same (1.00 to 1.12 times, 40 calls of
-//                       all layouts).  One sequence of 2500, 8000 and 32768 tokens
-//                       at GQ 4: 10.8, 15.7 and 24.7 us (11.4, 13.3 and 18.8 with
-//                       the longer chains; 150, 117 and 111 cut).
-// Rounding up to whole ranges makes the longest share total / (W - T) where the cut
-// list has total / W plus a segment's start, so the line lies where the two
-// differ by Units::seg (16 sequences of 2000 tokens, 128 tables: 16.5 against
-// 19.8 us; of 8192 tokens, over the line: 37 us cut).
+// table is cut into ceil(p / kOwnUnits) equal ranges of its p page units, one
+// workgroup each, a table in one range having no merge, wherever these ranges fit
+// the W resident workgroups.  kOwnUnits is a high page for every wave: the longest
+// chain of v_dot2 sums in a wave is then one page, the shortest there is, whatever
+// the cut list's would be.  Longer ranges would be faster (one sequence of 8000 and
+// 32768 tokens at GQ 4: 13.3 and 18.8 us with 2 sqrt(p) units, 15.7 and 24.7 now, 117
+// and 111 cut; 16 sequences of 2000 tokens, 128 tables: 16.1 with 98 units, 19.2 cut),
+// but a wave's weights are fp16 relative to the largest of its chain, so the
+// error against 64 bits grows with the chain: up to 1.39 times the cut list's where
+// the ranges were as long as it took to fit W workgroups, the same (1.00) here.
 template <int LI, int NW>
-constexpr int kOwnMin = NW * Units<LI>::hi;
-constexpr int kOwnMost = 20;
+constexpr int kOwnUnits = NW * Units<LI>::hi;
 
-template <int LI>
-__device__ __forceinline__ bool own_shares(long long total, int T, long long W)
+// Ranges of a table of `units` units (0: empty).
+template <int LI, int NW>
+__device__ __forceinline__ int own_ranges(long long units)
 {
-    return T < W && total * T <= Units<LI>::seg * W * (W - T);
+    return units > 0 ? ((int)units - Units<LI>::seg + kOwnUnits<LI, NW> - 1) / kOwnUnits<LI, NW> : 0;
 }
 
 template <int GQ, int LI>
@@ -1479,13 +1470,11 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
     const int t1 = t0 + per < T ? t0 + per : T;
     long long units[kKeep];
     long long mine = 0;
+    // thread 0 of workgroup t reads the arrival word of table t, for the claim below
+    const bool claim = threadIdx.x == 0 && k < T;
+    const unsigned long long word = claim ? arrive_peek(a.arrive + k) : 0ull;
     {
-        // all loads first (clamped to a valid table), then the units; thread 0
-        // also claims the arrival word of table blockIdx.x for this call (the
-        // shares of a split table arrive together: without the claim each
-        // retries a compare-and-swap against the others, 2 us per share)
-        const bool claim = threadIdx.x == 0 && k < T;
-        const unsigned long long word = claim ? arrive_peek(a.arrive + k) : 0ull;
+        // all loads first (clamped to a valid table), then the units
         int lh[kKeep], ll[kKeep];
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) {
@@ -1500,7 +1489,6 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
             // an empty table's output comes from workgroup t % W
             if (t0 + i < t1 && units[i] == 0 && (t0 + i) % W == k) write_empty_one(a, t0 + i, GQ);
         }
-        if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
     }
     for (int t = t0 + kKeep; t < t1; ++t) {
         const long long u = table_info<LI>(a, t).units;
@@ -1514,27 +1502,23 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
         sh.own_n = 0;
     }
     long long b_lo, b_hi;
-    if (own_shares<LI>(total, T, W)) {
-        const int room = (int)(W - T);
-        const int need = (int)((total + room - 1) / room);
-        const int least = need > kOwnMin<LI, NW> ? need : kOwnMin<LI, NW>;
-        auto shares_of = [&](long long un) {
-            if (un <= 0) return 0;
-            const int pu = (int)un - Units<LI>::seg;
-            const int root = (int)__builtin_sqrtf((float)pu);
-            const int len = root < kOwnMost ? root : kOwnMost;
-            const int quantum = len > least ? len : least;
-            return (pu + quantum - 1) / quantum;
-        };
+    // (the ranges hold all page units, so more than W * kOwnUnits of these never fit)
+    int own = 0, at = 0;
+    if (T <= W && total <= W * kOwnUnits<LI, NW> + (long long)T * Units<LI>::seg) {
         int cnt = 0;
-        for (int t = t0; t < t1; ++t) cnt += shares_of(t == t0 ? units[0] : table_info<LI>(a, t).units);
-        int all;
-        int at = block_excl_scan<int>(cnt, reinterpret_cast<int*>(sh.scan), &all);
-        if (k >= all) return;
+        for (int t = t0; t < t1; ++t) cnt += own_ranges<LI, NW>(t == t0 ? units[0] : table_info<LI>(a, t).units);
+        at = block_excl_scan<int>(cnt, reinterpret_cast<int*>(sh.scan), &own);
+    }
+    if (own <= W && own > 0) {
+        // The shares of a split table arrive together here: without the claim each
+        // retries a compare-and-swap against the others, 2 us per share.  (The cut
+        // list's arrive apart: the claim changed nothing there.)
+        if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
+        if (k >= own) return;
         long long u = before;
         for (int t = t0; t < t1; ++t) {
             const long long un = t == t0 ? units[0] : table_info<LI>(a, t).units;
-            const int n = shares_of(un);
+            const int n = own_ranges<LI, NW>(un);
             if (at <= k && k < at + n) {
                 const int c = (int)k - at, pu = (int)un - Units<LI>::seg;
                 sh.t_first = t;

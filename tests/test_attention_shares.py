@@ -27,36 +27,40 @@ def page_at_unit(x, ph, np_):
     return min(p, np_)
 
 
-def ranges_of(ph, pl, total, T, W, waves):
-    need = -(-total // (W - T))
+def own_ranges(ph, pl, waves):
     pu = HI * ph + LO * pl
-    quantum = max(need, waves * HI, min(20, int(math.sqrt(pu))))
-    n = -(-pu // quantum)
+    return -(-pu // (waves * HI))
+
+
+def ranges_of(ph, pl, waves):
+    pu, n = HI * ph + LO * pl, own_ranges(ph, pl, waves)
     cut = [0] + [SEG + c * pu // n for c in range(1, n + 1)]
     return [(page_at_unit(cut[c], ph, ph + pl), page_at_unit(cut[c + 1], ph, ph + pl)) for c in range(n)]
 
 
 def test_own_shares_cover_every_page_once():
+    """Every page lies in one range, the ranges fit the workgroups, and no range holds more
+    than one page per wave (the length of a wave's chain, on which the error depends)."""
     rng = random.Random(5)
     checked = 0
     for _ in range(4000):
         W, waves = rng.choice(((512, 8), (256, 12)))
-        T = int(math.exp(rng.uniform(0, math.log(W - 1))))
+        T = int(math.exp(rng.uniform(0, math.log(W))))
         top = int(math.exp(rng.uniform(0, math.log(3000))))
         tabs = [(rng.randint(0, top), rng.randint(0, top)) for _ in range(T)]
+        used = sum(own_ranges(a, b, waves) for a, b in tabs)
         total = sum(SEG + HI * a + LO * b for a, b in tabs if a + b)
-        if total * T > SEG * W * (W - T):
+        if used > W:
             continue
+        assert total <= W * waves * HI + T * SEG  # the kernel's test before it counts the ranges
         checked += 1
-        used = 0
         for a, b in tabs:
             if a + b == 0:
                 continue
-            r = ranges_of(a, b, total, T, W, waves)
-            used += len(r)
+            r = ranges_of(a, b, waves)
             assert r[0][0] == 0 and r[-1][1] == a + b
-            assert all(x[1] == y[0] and x[0] < x[1] for x, y in zip(r, r[1:]))
-        assert used <= W
+            assert all(x[1] == y[0] for x, y in zip(r, r[1:]))
+            assert all(0 < x[1] - x[0] <= waves for x in r)
     assert checked > 500
 
 
@@ -132,3 +136,37 @@ def test_own_shares_match_oracle(B, Hkv, gq, layout, lens):
         assert_attention_close(out.cpu().numpy(), lse.cpu().numpy(), ref, ref_lse, "own shares")
         first = first if first is not None else (out, lse)
         assert torch.equal(out, first[0]) and torch.equal(lse, first[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hkv,gq,pages", [(6, 8, 4, 80), (1, 1, 1, 8), (3, 8, 8, 96), (16, 8, 4, 32)])
+def test_own_shares_hold_a_page_per_wave(B, Hkv, gq, pages):
+    """Tables of high pages only, a multiple of the workgroup's waves (8, or 12 at GQ 8) each, whose
+    ranges fit the device: the shares are then num_splits = pages / waves equal ranges, merged in the
+    same order, so the results are the same bits.  With longer shares they are not."""
+    import torch
+    from gpu_util import dev_cache_from_oracle, layouts, t
+
+    from oracle import oracle as orc
+    from paper_2412_03131_amd import diffkv as dk
+
+    rng = np.random.default_rng(pages)
+    n = pages * 16
+    new_len = np.full(B, n, np.int32)
+    k = rng.standard_normal((B * n, Hkv, 128)).astype(np.float16).view(np.uint16)
+    v = rng.standard_normal((B * n, Hkv, 128)).astype(np.float16).view(np.uint16)
+    score = rng.random((B * n, Hkv)).astype(np.float32)
+    quota = np.tile(np.array([n, 0], np.int32), (B, Hkv, 1))
+    Lo, Ld = layouts(max_seq_len=n + 16)
+    oc = orc.Cache(Lo, B * Hkv * pages + 8, B, Hkv, ring=rng.permutation(B * Hkv * pages + 8))
+    orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+    assert oc.status[0] == 0
+    dc = dev_cache_from_oracle(Ld, oc)
+    q = rng.standard_normal((B, gq * Hkv, 128)).astype(np.float16).view(np.uint16)
+    waves = 12 if gq == 8 else 8
+    got = []
+    for splits in (-1, pages // waves):
+        print("case: page per wave B=%d gq=%d splits=%d" % (B, gq, splits), flush=True)
+        got.append(dk.decode_attention(dc, t(q), 1.0 / np.sqrt(128.0), num_splits=splits))
+        torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
