@@ -984,8 +984,10 @@ __device__ __forceinline__ void merge_parts(const AttnArgs& a, int t, const floa
     if (hh < GQ) {
         float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f;
         const float* first = base + hh * kPartStride;
-        if (nsl <= 4)
+        if (nsl <= 4)  // (eight for five slots: 0.4 us of a 19 us call)
             merge_chunks<4>(first, stride, nsl, lane, wrote, M, L, O0, O1);
+        else if (nsl <= 6)
+            merge_chunks<6>(first, stride, nsl, lane, wrote, M, L, O0, O1);
         else
             merge_chunks<8>(first, stride, nsl, lane, wrote, M, L, O0, O1);
         const long long row = (long long)b * a.Hq + h * GQ + hh;
