@@ -75,6 +75,10 @@ struct ColShape {
     static constexpr int kUnits = kTiles * kHeads;              // 32-row units of a stage
 };
 
+// With a zero addend the compiler may place the result over an operand that is not used
+// again.  An earlier kernel whose MFMA results lay over their B operand gave wrong
+// scores, so no kernel here relies on what the hardware does then: an operand of such a
+// product is named once more after it.
 __device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
@@ -274,6 +278,7 @@ __device__ __forceinline__ void rows_item(const PromptArgs& a, h8 (&sk)[2][kKeyB
                 f16v z;
                 for (int i = 0; i < 16; i++) z[i] = 0.0f;
                 acc[cb] = mfma32(af[0], qf[cb][0], z);
+                asm("" : "+v"(acc[cb]) : "v"(af[0]));  // (see mfma32)
                 for (int s = 1; s < 8; s++) acc[cb] = mfma32(af[s], qf[cb][s], acc[cb]);
             }
 #pragma unroll
