@@ -161,10 +161,11 @@ AttnWs attn_ws(int64_t B, int64_t Hq, int64_t Hkv, int64_t splits, int64_t worke
     return w;
 }
 
-// Prompt significance: sequence offsets and clamped lengths, work counters, row log2-sum-exps,
-// the column pass's sums per query segment.
+// Prompt significance: sequence offsets and clamped lengths, work counters and first items,
+// row log2-sum-exps, the column pass's sums per query segment.  (At most num_q_heads KV heads:
+// the size is asked for without them.)
 struct PromptWs {
-    int64_t off, nlen, ctr, lse2, part, total;
+    int64_t off, nlen, ctr, start, lse2, part, total;
 };
 
 PromptWs prompt_ws(int64_t B, int64_t Hq, int64_t total_new)
@@ -173,7 +174,8 @@ PromptWs prompt_ws(int64_t B, int64_t Hq, int64_t total_new)
     int64_t o = 0;
     w.off = o;  o = align256(o + B * 8);
     w.nlen = o; o = align256(o + B * 4);
-    w.ctr = o;  o = align256(o + 64);
+    w.ctr = o;  o = align256(o + 2 * kPromptQueues * kPromptCtrStride * 4);
+    w.start = o; o = align256(o + 2 * kPromptQueues * (B * Hq / (kPromptQueues * kPromptGroup) + 2) * 4);
     w.lse2 = o; o = align256(o + total_new * Hq * 4);
     w.part = o; o = align256(o + prompt_part_rows(B, Hq, total_new) * 4);
     w.total = o;
@@ -443,7 +445,8 @@ diffkv_status diffkv_prompt_significance(const diffkv_layout* layout, int32_t nu
     a.off = reinterpret_cast<long long*>(base + w.off);
     a.nlen = reinterpret_cast<int32_t*>(base + w.nlen);
     a.ctr = reinterpret_cast<int*>(base + w.ctr);
-    a.segs = prompt_segs(num_seqs, num_kv_heads, total_new);
+    a.start = reinterpret_cast<int*>(base + w.start);
+    a.segs = prompt_segs(num_seqs, num_q_heads, num_kv_heads, total_new, a.max_new);
     a.part = reinterpret_cast<float*>(base + w.part);
     a.lse2 = reinterpret_cast<float*>(base + w.lse2);
     hipError_t e = launch_prompt_significance(a, num_q_heads / num_kv_heads, static_cast<hipStream_t>(stream));

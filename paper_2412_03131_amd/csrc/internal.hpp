@@ -186,10 +186,20 @@ struct PromptArgs {
     long long* off;      // [B] first row of each sequence (workspace)
     int32_t* nlen;       // [B] rows of each sequence, clamped to max_new and total_new (workspace)
     float* lse2;         // [total_new][Hq] row log2-sum-exp (workspace)
-    int* ctr;            // [16] work counters of the two passes (workspace)
+    int* ctr;            // [2][kPromptQueues] work counters of the two passes, kPromptCtrStride apart (workspace)
+    int* start;          // [2][kPromptQueues][groups + 1] first items (workspace)
+    int groups;          // groups of pairs per list
+    int once[2];         // the passes with one workgroup per item
+    int row_pos, row_groups;  // the row pass's positions per block and head groups
     int segs;            // query segments per key block of the column pass
     float* part;         // [segs][total_new][Hkv] the segments' sums, segs > 1 (workspace)
 };
+
+// Lists of work items (one per XCD), pairs per group of a list, ints between two counters
+// (a cache line each: sixteen in one line took 60 us to find empty).
+constexpr int kPromptQueues = 8;
+constexpr int kPromptGroup = 8;
+constexpr int kPromptCtrStride = 32;
 
 // Query segments per 256-key block of the column pass: where there are fewer key
 // blocks than would keep the device busy, each block's queries are cut, down to
@@ -198,12 +208,21 @@ struct PromptArgs {
 // query heads, 241 us cut).  A sum over segments replaces the direct store.
 constexpr int kPromptBusyBlocks = 2048;
 constexpr int kPromptMaxSegs = 8;
-inline int prompt_segs(long long B, long long Hkv, long long total_new)
+constexpr int kPromptFewStagesBlocks = 512;
+// No more than the longest prompt has stages of query positions (128 at one query head
+// per KV head, 64 at two, else 32), and for prompts of a few stages only as many as
+// run at once: a stage is then worth less than the launch that adds the segments (256
+// prompts of 100 tokens, 4 / 1 heads: 21.0 us in four segments, 17.6 whole).
+inline int prompt_segs(long long B, long long Hq, long long Hkv, long long total_new, long long max_new)
 {
     const long long blocks = (total_new / 256 + B) * Hkv;
     if (blocks <= 0) return 1;
-    const long long s = (kPromptBusyBlocks + blocks - 1) / blocks;
-    return (int)(s < kPromptMaxSegs ? s : kPromptMaxSegs);
+    long long s = (kPromptBusyBlocks + blocks - 1) / blocks;
+    if (s > kPromptMaxSegs) s = kPromptMaxSegs;
+    const long long g = Hq / Hkv, stage = g == 1 ? 128 : (g == 2 ? 64 : 32), stages = (max_new + stage - 1) / stage;
+    if (s > stages) s = stages;
+    if (stages <= kPromptMaxSegs && s > kPromptFewStagesBlocks / blocks) s = kPromptFewStagesBlocks / blocks;
+    return (int)(s < 1 ? 1 : s);
 }
 // Most values the segments' sums take for any number of KV heads (Hq / 8 .. Hq):
 // the workspace size is not told it.

@@ -57,7 +57,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // Row pass: a wave takes 64 query positions of one head, a workgroup all heads
 // of kPos positions, or half of seven or eight heads (four waves for one or two
-// heads, one wave per head above).  158 VGPRs: three waves per SIMD.
+// heads, one wave per head above).  168 VGPRs: three waves per SIMD.
 template <int G>
 struct RowShape {
     static constexpr int kGroups = G >= 7 ? 2 : 1;               // head groups
@@ -91,51 +91,100 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // quiets an operand the compiler has not seen computed)
 __device__ __forceinline__ float max_med(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf()); }
 
-// Work items: (pair = sequence and KV head, block), handed out by eight counters,
-// one queue per XCD (consecutive workgroups go round-robin over the XCDs, so
-// workgroup i starts on queue i % 8; a queue that has run out passes it on to the
-// next).  Queue x holds pairs x, x + 8, ..., eight of them at a time, block-major
-// with the heaviest block (0) first: the blocks of a pair run close together and
-// share its rows in one XCD's L2, and every queue has pairs from all over the
-// batch.  The items vary by a factor of N in work, and workgroups are dispatched
-// strictly in order, over the shader engines in turn: one workgroup per item
-// kept 62 % of the waves resident (column pass, 64 prompts of 1k-4k tokens), so
-// each resident workgroup takes items until there are none.  Which workgroup
-// takes an item does not change its result.
-constexpr int kQueues = 8;
-constexpr int kQueuePairs = 8;
-struct WorkQueue {
-    int* ctr;      // [kQueues] items handed out
-    int x, tried;  // current queue, queues found empty
-    int pairs, nblk;
-    // next item of a nonempty block (live(pair, blk)), or false: one thread
-    template <typename Live>
-    __device__ __forceinline__ bool next(int& pair, int& blk, Live live)
+// Work items: (pair = sequence and KV head, block), in eight lists, one per XCD
+// (consecutive workgroups go round-robin over the XCDs, so workgroup i takes item i / 8
+// of list i % 8).  List x holds pairs x, x + 8, ..., eight of them at a time (a group),
+// block-major with the heaviest block (0) first: the blocks of a pair run close
+// together and share its rows in one XCD's L2, and every list has pairs from all
+// over the batch.  Which workgroup takes an item does not change its result.
+//
+// A pass of few items (PromptArgs::once) has a workgroup per item.  The items vary by a
+// factor of N in work, and workgroups are dispatched strictly in order, over the
+// shader engines in turn: with long prompts one workgroup per item kept 62 % of the
+// waves resident (column pass, 64 prompts of 1k-4k tokens).  So in a pass of many items
+// each resident workgroup goes on with further items of its list, handed out by a
+// counter, then of the others, until there are none; a group there has the blocks of
+// its own longest prompt (ps_offsets): with those of the batch's longest for every
+// pair most items of one prompt of 4096 and 1023 of 16 tokens were empty (32 / 8 heads:
+// 7.6 ms; 2.1 with a workgroup per item, 0.5 so).
+struct WorkItems {
+    const int* start;  // [kPromptQueues][groups + 1] first item of each group, the list's items last
+    int* ctr;          // items handed out beyond the workgroups' first ones
+    int once, pairs, groups;
+    int nblk;          // blocks of every pair, once
+    __device__ __forceinline__ int first_items(int x) const { return ((int)gridDim.x - x + kPromptQueues - 1) / kPromptQueues; }
+    __device__ __forceinline__ int items(int x) const { return start[x * (groups + 1) + groups]; }
+    // Item k of list x: pair, block, blocks of the pair's group; false past the list's end.  Whole waves.
+    __device__ __forceinline__ bool locate(int x, int k, int& pair, int& blk, int& blocks) const
     {
-        while (tried < kQueues) {
-            const int np = (pairs - x + kQueues - 1) / kQueues;
-            const long long n = np > 0 ? (long long)np * nblk : 0;
-            const long long k = n > 0 ? atomicAdd(ctr + x, 1) : 0;
-            if (k >= n) {
-                x = (x + 1) % kQueues;
-                ++tried;
-                continue;
-            }
-            const int g = (int)(k / (kQueuePairs * nblk)), rem = (int)(k - (long long)g * kQueuePairs * nblk);
-            const int w = min(kQueuePairs, np - g * kQueuePairs);
-            blk = rem / w;
-            pair = x + kQueues * (g * kQueuePairs + rem % w);
-            if (live(pair, blk)) return true;
+        if (once) {  // all pairs are one group
+            const int i = k * kPromptQueues + x;
+            blocks = nblk;
+            blk = i / pairs;
+            pair = i - blk * pairs;
+            return true;
         }
-        return false;
+        const int* sx = start + x * (groups + 1);
+        if (k >= sx[groups]) return false;
+        const int lane = threadIdx.x & (kWave - 1);
+        int g = 0;
+        for (int len = groups; len > 1;) {  // the last group that starts at or before k
+            const int step = (len + kWave - 1) / kWave, at = lane * step;
+            const int c = __popcll(__builtin_amdgcn_ballot_w64(at < len && sx[g + (at < len ? at : 0)] <= k)) - 1;
+            g += c * step;
+            len = min(step, len - c * step);
+        }
+        const int first = sx[g], np = (pairs - x + kPromptQueues - 1) / kPromptQueues;
+        const int w = min(kPromptGroup, np - g * kPromptGroup);
+        blocks = (sx[g + 1] - first) / w;
+        blk = (k - first) / w;
+        pair = x + kPromptQueues * (g * kPromptGroup + (k - first) % w);
+        return true;
+    }
+    // The next item to take, from list x on (one whole wave); false: none is left.
+    __device__ __forceinline__ bool next(int& x, int& k) const
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        for (;;) {
+            int got = 0;
+            if (lane == 0) got = atomicAdd(ctr + x * kPromptCtrStride, 1);
+            k = first_items(x) + __builtin_amdgcn_readfirstlane(got);
+            if (k < items(x)) return true;
+            // which lists have items: all eight counters at once
+            bool left = false;
+            if (lane < kPromptQueues)
+                left = first_items(lane) + __hip_atomic_load(ctr + lane * kPromptCtrStride, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT) < items(lane);
+            const unsigned m = (unsigned)__builtin_amdgcn_ballot_w64(left);
+            if (!m) return false;
+            x = (x + __builtin_ctz(m >> x | m << (kPromptQueues - x))) % kPromptQueues;
+        }
     }
 };
 
-__device__ __forceinline__ h8 zero8()
+// f(pair, block, blocks of the pair's group) for the workgroup's items.
+template <typename F>
+__device__ __forceinline__ void for_items(const WorkItems& wi, F&& f)
 {
-    h8 z;
-    for (int i = 0; i < 8; i++) z[i] = (_Float16)0.0f;
-    return z;
+    __shared__ int s_next[2];
+    int x = blockIdx.x % kPromptQueues, k = blockIdx.x / kPromptQueues;
+    for (;;) {
+        int pair, blk, blocks;
+        if (wi.locate(x, k, pair, blk, blocks)) f(pair, blk, blocks);
+        if (wi.once) return;
+        __syncthreads();  // s_next and the item's LDS are written again
+        if (wave_index() == 0) {
+            if (!wi.next(x, k)) x = -1;
+            if (threadIdx.x == 0) {
+                s_next[0] = x;
+                s_next[1] = k;
+            }
+        }
+        __syncthreads();
+        x = __builtin_amdgcn_readfirstlane(s_next[0]);
+        k = __builtin_amdgcn_readfirstlane(s_next[1]);
+        if (x < 0) return;
+    }
 }
 
 // LDS rows of 16 chunks without padding (loads with an LDS destination write
@@ -196,7 +245,7 @@ __global__ __launch_bounds__(kPsThreads) void ps_offsets(PromptArgs a)
 {
     __shared__ long long part[kPsThreads];
     const int tid = threadIdx.x;
-    if (tid < 2 * kQueues) a.ctr[tid] = 0;  // the passes' work queues
+    if (tid < 2 * kPromptQueues) a.ctr[tid * kPromptCtrStride] = 0;
     const int per = (a.B + kPsThreads - 1) / kPsThreads;
     const int b0 = tid * per, b1 = min(a.B, b0 + per);
     long long s = 0;
@@ -217,19 +266,45 @@ __global__ __launch_bounds__(kPsThreads) void ps_offsets(PromptArgs a)
         a.nlen[b] = (int)(room <= 0 ? 0 : (n < room ? n : room));
         off += n;
     }
+    if (a.once[0] && a.once[1]) return;
+    // first items of every list's groups, for both passes: a wave per list
+    __syncthreads();
+    const int lane = tid & (kWave - 1), pairs = a.B * a.Hkv;
+    for (int x = wave_index(); x < kPromptQueues; x += kPsThreads / kWave) {
+        int before[2] = {0, 0};
+        for (int g0 = 0; g0 <= a.groups; g0 += kWave) {
+            const int g = g0 + lane, p0 = x + kPromptQueues * kPromptGroup * g;
+            int n = 0, w = 0;
+            if (g < a.groups) {
+                for (int j = 0; j < kPromptGroup; j++) {
+                    const int p = p0 + kPromptQueues * j;
+                    if (p < pairs) {
+                        n = max(n, a.nlen[p / a.Hkv]);
+                        w++;
+                    }
+                }
+            }
+            const int items[2] = {(n + a.row_pos - 1) / a.row_pos * a.row_groups * w,
+                                  (n + kColKeys - 1) / kColKeys * a.segs * w};
+            for (int i = 0; i < 2; i++) {
+                const int incl = wave_incl_scan(items[i]);
+                if (g <= a.groups) a.start[(i * kPromptQueues + x) * (a.groups + 1) + g] = before[i] + incl - items[i];
+                before[i] += __builtin_amdgcn_readlane(incl, kWave - 1);
+            }
+        }
+    }
 }
 
 // Pass 1: lse2[row][hq] = log2 sum_{p <= j} exp2(scale_log2 * q_j . k_p).
 // One item: a pair's block of query positions (blk 0 the last, the heaviest).
 template <int G>
-__device__ __forceinline__ void rows_item(const PromptArgs& a, h8 (&sk)[2][kKeyBlock][kChunks], int bh, int blk, int nqb)
+__device__ __forceinline__ void rows_item(const PromptArgs& a, h8 (&sk)[2][kKeyBlock][kChunks], int bh, int qb, int hg)
 {
     using R = RowShape<G>;
     constexpr int kWaves = R::kWaves, PB = R::kPos;
-    const int qb = nqb - 1 - blk / R::kGroups, hg = blk % R::kGroups;
     const int b = bh / a.Hkv, h = bh - b * a.Hkv;
-    const int N = a.nlen[b];
-    const long long off = a.off[b];
+    const int N = __builtin_amdgcn_readfirstlane(a.nlen[b]);
+    const long long off = read_lane<long long>(a.off[b], 0);  // (scalar: the loads' base)
     const int q0 = qb * PB;
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -243,9 +318,10 @@ __device__ __forceinline__ void rows_item(const PromptArgs& a, h8 (&sk)[2][kKeyB
     // B operands: 32 positions per block, k = 16 s + 8 half ..
     h8 qf[2][8];
     for (int cb = 0; cb < 2; cb++) {
-        const int j = wq0 + 32 * cb + col;
-        const h8* src = reinterpret_cast<const h8*>(a.q + ((off + j) * a.Hq + h * G + t) * kD);
-        for (int s = 0; s < 8; s++) qf[cb][s] = j < N && t < G ? src[2 * s + half] : zero8();
+        // (positions past the prompt repeat its last, heads past the group its last: not written)
+        const int j = min(wq0 + 32 * cb + col, N - 1);
+        const h8* src = reinterpret_cast<const h8*>(a.q + ((off + j) * a.Hq + h * G + min(t, G - 1)) * kD);
+        for (int s = 0; s < 8; s++) qf[cb][s] = src[2 * s + half];
     }
     float m[2] = {-1e30f, -1e30f}, sum[2] = {0.0f, 0.0f};
 
@@ -332,22 +408,12 @@ __global__ __launch_bounds__(RowShape<G>::kWaves * kWave, 3) void ps_rows(Prompt
 {
     using R = RowShape<G>;
     __shared__ h8 sk[2][kKeyBlock][kChunks];
-    __shared__ int s_item[2];
-    const int nqb = (a.max_new + R::kPos - 1) / R::kPos;
-    WorkQueue queue = {a.ctr, (int)(blockIdx.x % kQueues), 0, a.B * a.Hkv, nqb * R::kGroups};
-    for (;;) {
-        if (threadIdx.x == 0) {
-            int pair = -1, blk = 0;
-            const bool any = queue.next(pair, blk, [&](int p, int k) { return (nqb - 1 - k / R::kGroups) * R::kPos < a.nlen[p / a.Hkv]; });
-            s_item[0] = any ? pair : -1;
-            s_item[1] = blk;
-        }
-        __syncthreads();
-        const int bh = __builtin_amdgcn_readfirstlane(s_item[0]), blk = __builtin_amdgcn_readfirstlane(s_item[1]);
-        if (bh < 0) return;
-        rows_item<G>(a, sk, bh, blk, nqb);
-        __syncthreads();  // s_item and the stages are written again
-    }
+    const WorkItems wi = {a.start, a.ctr, a.once[0], a.B * a.Hkv, a.groups,
+                          (a.max_new + R::kPos - 1) / R::kPos * R::kGroups};
+    for_items(wi, [&](int pair, int blk, int blocks) {  // blk 0 the last positions
+        const int qb = (blocks - 1 - blk) / R::kGroups;
+        if (qb * R::kPos < a.nlen[pair / a.Hkv]) rows_item<G>(a, sk, pair, qb, blk % R::kGroups);
+    });
 }
 
 // Pass 2: score[row][h] = (1 / (N - p)) sum_{j >= p} max_t exp2(scale_log2 * q_j,t . k_p - lse2[j][t]).
@@ -365,8 +431,8 @@ __device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, i
     using S = ColShape<G>;
     constexpr int QI = 32 * S::kTiles;               // query positions per stage
     const int b = bh / a.Hkv, h = bh - b * a.Hkv;
-    const int N = a.nlen[b];
-    const long long off = a.off[b];
+    const int N = __builtin_amdgcn_readfirstlane(a.nlen[b]);
+    const long long off = read_lane<long long>(a.off[b], 0);  // (scalar: the loads' base)
     const int k0 = kb * kColKeys;
 
     const int tid = threadIdx.x;
@@ -380,9 +446,9 @@ __device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, i
     // B operands: 32 keys per block, k = 16 s + 8 half ..
     h8 kf[2][8];
     for (int cb = 0; cb < 2; cb++) {
-        const int p = wk0 + 32 * cb + col;
+        const int p = min(wk0 + 32 * cb + col, N - 1);  // (keys past the prompt repeat its last: not written)
         const h8* src = reinterpret_cast<const h8*>(a.k + ((off + p) * a.Hkv + h) * kD);
-        for (int s = 0; s < 8; s++) kf[cb][s] = p < N ? src[2 * s + half] : zero8();
+        for (int s = 0; s < 8; s++) kf[cb][s] = src[2 * s + half];
     }
     float cs[2] = {0.0f, 0.0f};
 
@@ -489,22 +555,11 @@ template <int G>
 __global__ __launch_bounds__(kPsThreads, 2) void ps_cols(PromptArgs a)
 {
     __shared__ ColLds<G> lds;
-    __shared__ int s_item[2];
-    const int nkb = (a.max_new + kColKeys - 1) / kColKeys;
-    WorkQueue queue = {a.ctr + kQueues, (int)(blockIdx.x % kQueues), 0, a.B * a.Hkv, nkb * a.segs};
-    for (;;) {
-        if (threadIdx.x == 0) {
-            int pair = -1, blk = 0;
-            const bool any = queue.next(pair, blk, [&](int p, int k) { return k / a.segs * kColKeys < a.nlen[p / a.Hkv]; });
-            s_item[0] = any ? pair : -1;
-            s_item[1] = blk;
-        }
-        __syncthreads();
-        const int bh = __builtin_amdgcn_readfirstlane(s_item[0]), blk = __builtin_amdgcn_readfirstlane(s_item[1]);
-        if (bh < 0) return;
-        cols_item<G>(a, lds, bh, blk / a.segs, blk % a.segs);
-        __syncthreads();  // s_item and the stages are written again
-    }
+    const WorkItems wi = {a.start + kPromptQueues * (a.groups + 1), a.ctr + kPromptQueues * kPromptCtrStride, a.once[1],
+                          a.B * a.Hkv, a.groups, (a.max_new + kColKeys - 1) / kColKeys * a.segs};
+    for_items(wi, [&](int pair, int blk, int) {
+        if (blk / a.segs * kColKeys < a.nlen[pair / a.Hkv]) cols_item<G>(a, lds, pair, blk / a.segs, blk % a.segs);
+    });
 }
 
 // The segments' sums of each (row, KV head), in order, over the row's queries.
@@ -522,39 +577,56 @@ __global__ __launch_bounds__(kPsThreads) void ps_finish(PromptArgs a)
 
 namespace {
 
-template <int G>
-hipError_t launch_prompt_g(const PromptArgs& a, int cus, hipStream_t st)
+// Workgroups of a pass: one per item up to `most` times as many as are resident at once
+// (per_cu per CU), or while no prompt is long (their items are alike), else as many as
+// are resident.  Handing items out costs a round trip to the counters and two barriers per
+// item, one workgroup per item the waves that the order of dispatch leaves out.  Row pass,
+// at 32 / 8 heads: 64 prompts of 700 tokens, 7 times the resident, 314 us one per item and 338
+// handed out; 64 of 1k-4k, 43 times, 5.07 and 4.75 ms.  Column pass: 64 of 700 at 64 / 8
+// heads, 6 times, 318 and 302 us; 64 of 1k-4k, 16 times, 4.75 and 4.41 ms; 2000 of 64
+// tokens, 31 times, 640 and 686 us with the row pass.
+unsigned pass_grid(long long items, int max_new, int most, int cus, int per_cu, int* once)
 {
-    const long long pairs = (long long)a.B * a.Hkv;
-    hipError_t e;
-    if (!a.lse) {
-        const long long blocks = pairs * ((a.max_new + RowShape<G>::kPos - 1) / RowShape<G>::kPos);
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        const long long grid = min(blocks * RowShape<G>::kGroups, (long long)cus * RowShape<G>::kPerCu);
-        if ((e = launch1(ps_rows<G>, (unsigned)grid, RowShape<G>::kWaves * kWave, st, a)) != hipSuccess) return e;
-    }
-    const long long blocks = pairs * ((a.max_new + kColKeys - 1) / kColKeys);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    e = launch1(ps_cols<G>, (unsigned)min(blocks * a.segs, (long long)cus * 2), kPsThreads, st, a);
+    const long long resident = (long long)cus * per_cu;
+    *once = items <= most * resident || max_new <= 512;
+    return (unsigned)(*once ? items : resident);
+}
+
+template <int G>
+hipError_t launch_prompt_g(PromptArgs& a, int cus, hipStream_t st)
+{
+    using R = RowShape<G>;
+    const int pairs = a.B * a.Hkv;
+    const long long rblk = (a.max_new + R::kPos - 1) / R::kPos, cblk = (a.max_new + kColKeys - 1) / kColKeys;
+    if (a.lse == nullptr && pairs * rblk > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (pairs * cblk > 0x7fffffffLL) return hipErrorInvalidValue;
+    a.row_pos = R::kPos;
+    a.row_groups = R::kGroups;
+    a.groups = (pairs + kPromptQueues * kPromptGroup - 1) / (kPromptQueues * kPromptGroup);
+    const unsigned rgrid = pass_grid(pairs * rblk * R::kGroups, a.max_new, 16, cus, R::kPerCu, &a.once[0]);
+    const unsigned cgrid = pass_grid(pairs * cblk * a.segs, a.max_new, 4, cus, 2, &a.once[1]);
+    if (a.lse) a.once[0] = 1;  // (no row pass)
+    hipError_t e = launch1(ps_offsets, 1, kPsThreads, st, a);
+    if (e == hipSuccess && !a.lse) e = launch1(ps_rows<G>, rgrid, R::kWaves * kWave, st, a);
+    if (e == hipSuccess) e = launch1(ps_cols<G>, cgrid, kPsThreads, st, a);
     if (e != hipSuccess || a.segs == 1) return e;
     const long long rows = (long long)a.max_new * a.Hkv;
     const unsigned gx = (unsigned)min((rows + kPsThreads - 1) / kPsThreads, 64LL);
-    void* args[] = {const_cast<PromptArgs*>(&a)};
+    void* args[] = {&a};
     return hipLaunchKernel(reinterpret_cast<const void*>(ps_finish), dim3(gx, (unsigned)a.B), dim3(kPsThreads), args, 0, st);
 }
 
 }  // namespace
 
-hipError_t launch_prompt_significance(const PromptArgs& a, int g, hipStream_t st)
+hipError_t launch_prompt_significance(const PromptArgs& args, int g, hipStream_t st)
 {
+    PromptArgs a = args;
     if (a.B <= 0 || a.max_new <= 0) return hipSuccess;
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cus < 1) cus = 1;
-    e = launch1(ps_offsets, 1, kPsThreads, st, a);
-    if (e != hipSuccess) return e;
     switch (g) {
     case 1: return launch_prompt_g<1>(a, cus, st);
     case 2: return launch_prompt_g<2>(a, cus, st);

@@ -1,6 +1,6 @@
 """Prompt-phase significance where its two passes branch: query segments of the column
-pass (fewer stages than segments, one segment, a sum over several), more pairs than the
-work queues take at a time with empty blocks between, head groups of the row pass, and
+pass (fewer stages than segments, one segment, a sum over several), pairs no multiple of
+eight with empty blocks between, head groups of the row pass, and
 logits that jump past what the row pass's running max absorbs.  Against the oracle,
 with the tolerance of fp32 logits (relative 5e-5)."""
 import numpy as np
@@ -26,7 +26,7 @@ def _run(new_len, q, k, lse=None):
     ((31,), 1, 1),                         # fewer stages than segments
     ((33, 0, 255, 256, 257), 3, 7),        # head groups of 4 + 3, block edges
     ((700,), 2, 8),                        # two head groups, several stages per segment
-    ((5, 130, 1, 64, 97) * 5, 9, 2),       # 225 pairs: four rounds of the queues, no multiple of eight
+    ((5, 130, 1, 64, 97) * 5, 9, 2),       # 225 pairs, no multiple of eight
     ((129,) * 260, 8, 1),                  # 2080 key blocks: one segment
 ])
 def test_segments_and_queues(lens, Hkv, g):
