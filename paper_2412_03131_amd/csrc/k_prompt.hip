@@ -25,8 +25,11 @@
 //            key, whose sum stays in the lane to the end: no atomics, a fixed
 //            order.  Few key blocks are cut into query segments (prompt_segs).
 //
-// Both stage the next tile while they compute one, by loads with an LDS
-// destination.  The MFMA results stay in VGPRs (two or three waves per SIMD
+// Both ask for the next tile before they compute one, by loads with an LDS
+// destination.  They overlap across waves more than within one: in most instances
+// the compiler's first use of the fragments loaded before the loop comes after those
+// loads and waits for them too (for any load still counted, as it cannot see the
+// wait in the inline asm of stage_ready).  The MFMA results stay in VGPRs (two or three waves per SIMD
 // bound the registers to 256; with more, every result went through an AGPR
 // copy).
 //
@@ -87,8 +90,9 @@ __device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// max(a, b) as the median of a, b and infinity: one instruction (fmaxf first
-// quiets an operand the compiler has not seen computed)
+// max(a, b) as the median of a, b and infinity.  The compiler makes it a maximum again and
+// at GQ 2, 4, 6, 7 and 8 quiets both operands first (64 to 128 extra instructions in the
+// column pass's loop); NaN operands are ignored either way.
 __device__ __forceinline__ float max_med(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf()); }
 
 // Work items: (pair = sequence and KV head, block), in eight lists, one per XCD
@@ -455,6 +459,8 @@ __device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, i
     const int nq = (N - k0 + QI - 1) / QI;  // stages [it0, it1) of the segment's positions
     const int it0 = (int)((long long)seg * nq / a.segs), it1 = (int)((long long)(seg + 1) * nq / a.segs);
     float pl = 0.0f;
+    bool pl_off = false;
+    const float lse_scale = (a.lse ? -kLog2e : -1.0f) * inv_c;
     const long long stride = (long long)a.Hq * kD;
     const uint32_t v0 = lane_offset(stride);
     // Stage s = it * kGroups + g: positions k0 + it * QI .., heads g * kHeads ..
@@ -476,8 +482,9 @@ __device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, i
         if (tid < S::kUnits * 32) {
             const int u = tid >> 5, tile = u / S::kHeads, t = u - tile * S::kHeads;
             const int j = j0 + 32 * tile + (tid & 31);
-            const long long e = (off + j) * a.Hq + h * G + h0 + t;
-            pl = j >= N || t >= nh ? __builtin_huge_valf() : (a.lse ? a.lse[e] * kLog2e : a.lse2[e]);
+            const long long e = (off + min(j, N - 1)) * a.Hq + h * G + h0 + min(t, nh - 1);
+            pl_off = j >= N || t >= nh;
+            pl = (a.lse ? a.lse : a.lse2)[e];  // (scaled where it is used: no wait for the loads here)
         }
     };
     // last positions first: the key blocks of one (sequence, KV head), which run at
@@ -488,7 +495,7 @@ __device__ __forceinline__ void cols_item(const PromptArgs& a, ColLds<G>& lds, i
         f16v mx[S::kTiles][2];
 #pragma unroll
         for (int g = 0; g < S::kGroups; g++) {
-            if (tid < S::kUnits * 32) lds.bias[buf][tid >> 5][tid & 31] = -pl * inv_c;
+            if (tid < S::kUnits * 32) lds.bias[buf][tid >> 5][tid & 31] = pl_off ? -__builtin_huge_valf() : pl * lse_scale;
             stage_ready();
             if (g + 1 < S::kGroups) stage(it, g + 1, buf ^ 1);
             else if (it > it0) stage(it - 1, 0, buf ^ 1);
