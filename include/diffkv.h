@@ -169,7 +169,8 @@ diffkv_status diffkv_workspace_size(int32_t op, const diffkv_layout* layout,
  *            sum of new_len[0..b).  Must sum to total_new with every entry in
  *            [0, max_new], else DIFFKV_ST_BAD_INPUT is raised and nothing
  *            changes.
- *   k, v     device fp16 [total_new][num_kv_heads][head_dim].
+ *   k, v     device fp16 [total_new][num_kv_heads][head_dim], of any alignment
+ *            an fp16 value may have (16 bytes make the loads cheapest).
  *   score    device fp32 [total_new][num_kv_heads]: significance (not NaN).
  *   quota    device int32 [num_seqs][num_kv_heads][2] = {n_high, n_low}, or
  *            NULL.  Quota form: the non-window new tokens are ranked by

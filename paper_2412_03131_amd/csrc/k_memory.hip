@@ -434,6 +434,10 @@ struct PageImage {
     uint4 b[kPageMax / 16];
 };
 
+// Eight fp16 values of the caller's k or v, which may start anywhere an fp16 value may:
+// still one 16-byte load (the device takes unaligned ones), but never assumed aligned.
+typedef uint32_t Fp16x8 __attribute__((ext_vector_type(4), aligned(2)));
+
 // One page job, by one wave: resolve the page ID (a new page from the table's
 // ring region), quantize the job's tokens, write them, zero a fresh page's
 // unused bytes.  Lane = (row of 16, eight dims): row r takes the TT/4 page
@@ -489,8 +493,8 @@ __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDes
             if (step_on(i0 + i)) {
                 const int jt = __shfl(j, NS * row + i0 + i, kWave);
                 const long long at = ((long long)(off_b + jt) * H + h) * (kD / 8) + l16;
-                kx[i] = reinterpret_cast<const uint4*>(a.k)[at];
-                vx[i] = reinterpret_cast<const uint4*>(a.v)[at];
+                kx[i] = __builtin_bit_cast(uint4, reinterpret_cast<const Fp16x8*>(a.k)[at]);
+                vx[i] = __builtin_bit_cast(uint4, reinterpret_cast<const Fp16x8*>(a.v)[at]);
             }
         }
     };

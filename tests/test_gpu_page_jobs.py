@@ -55,3 +55,35 @@ def test_page_jobs_bitexact(layout, B, Hkv):
         dk.quantize_append(dc, t(new_len), t(k), t(v), t(score), quota=t(quota), total_new=rows, max_new=most)
         assert oc.status[0] == 0
         assert_state_equal(dc, oc, what="layout %d step %d" % (layout, step))
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3, 4, 7])
+def test_rows_of_any_alignment(shift):
+    """k and v that start `shift` fp16 values past a 16-byte boundary (a slice of a larger buffer)."""
+    import torch
+    rng = np.random.default_rng(shift)
+    Lo, Ld = layouts(max_seq_len=192)
+    B, Hkv = 3, 2
+    pages = B * Hkv * 16
+    oc = orc.Cache(Lo, pages, B, Hkv, ring=rng.permutation(pages))
+    dc = dev_cache_from_oracle(Ld, oc)
+    for step, most in enumerate((70, 1, 19)):
+        new_len = np.array([most, most // 2, 1], np.int32)
+        rows = int(new_len.sum())
+        k, v = edge_values(rng, rows, Hkv), edge_values(rng, rows, Hkv)
+        score = rng.random((rows, Hkv)).astype(np.float32)
+        quota = np.repeat(np.stack([new_len // 2, new_len - new_len // 2], 1)[:, None], Hkv, 1).astype(np.int32)
+
+        def shifted(x):
+            buf = torch.zeros(x.size + 16, dtype=torch.int16, device="cuda")
+            out = buf[shift:shift + x.size].view(x.shape)
+            out.copy_(t(x))
+            assert out.data_ptr() % 16 == 2 * shift
+            return out
+
+        print("case: page jobs shift=%d step=%d" % (shift, step), flush=True)
+        orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+        dk.quantize_append(dc, t(new_len), shifted(k), shifted(v), t(score), quota=t(quota), total_new=rows,
+                           max_new=most)
+        assert oc.status[0] == 0
+        assert_state_equal(dc, oc, what="shift %d step %d" % (shift, step))
