@@ -87,3 +87,68 @@ def test_rows_of_any_alignment(shift):
                            max_new=most)
         assert oc.status[0] == 0
         assert_state_equal(dc, oc, what="shift %d step %d" % (shift, step))
+
+
+def model_group(x, bits):
+    """(scale, zero, codes) of one group: NaN ignored in the extremes, NaN quotients code 0."""
+    with np.errstate(all="ignore"):
+        f = x.astype(np.float32) + np.float32(0)
+        ok = f[~np.isnan(f)]
+        mn, mx = (ok.min(), ok.max()) if ok.size else (np.float32(np.nan),) * 2
+        lb = np.float32(2 ** bits - 1)
+        s, z = ((mx - mn) / lb).astype(np.float16), mn.astype(np.float16)
+        if s == 0:
+            return s, z, np.zeros(f.size, np.int64)
+        q = np.rint((f - z.astype(np.float32)) / s.astype(np.float32))
+        q[np.isnan(q)] = 0
+        return s, z, np.clip(q, 0, lb).astype(np.int64)
+
+
+def codes_of(seg, count, bits):
+    """`count` codes of `bits` bits from a segment's rows of bytes, lowest first."""
+    return np.unpackbits(seg, axis=-1, bitorder="little")[..., :count * bits].reshape(*seg.shape[:-1], count, bits) @ \
+        (1 << np.arange(bits))
+
+
+@pytest.mark.parametrize("layout", range(4))
+def test_infinities_and_nan(layout):
+    """Groups with infinities and NaN: an infinity makes the scale infinite and every code 0, NaN counts
+    in no extreme and gets code 0, and the groups beside them are untouched by either."""
+    import torch
+    rng = np.random.default_rng(40 + layout)
+    Lo, Ld = layouts(max_seq_len=192, **LAYOUTS[layout])
+    n = 24
+    k, v = (rng.standard_normal((n, 1, 4, 32)).astype(np.float16) for _ in range(2))
+    for x in (k, v):
+        kind = rng.integers(0, 8, (n, 1, 4))
+        at = rng.random(x.shape) < 0.1
+        for i, values in enumerate(((np.inf,), (-np.inf,), (np.nan,), (np.inf, -np.inf, np.nan))):
+            pick = at & (kind == i)[..., None]
+            x[pick] = rng.choice(values, int(pick.sum())).astype(np.float16)
+        x[kind == 4] = np.float16(np.nan)
+    score = np.arange(n, 0, -1).astype(np.float32)[:, None]
+    new_len = np.array([n], np.int32)
+    half = n // 2  # one page per section
+    quota = np.array([[[half, half]]], np.int32)
+    dc = dk.Cache(Ld, 8, 1, 1)
+    bits = lambda x: torch.from_numpy(x.view(np.int16).reshape(n, 1, 128).copy()).cuda()
+    print("case: page jobs, infinities and NaN, layout=%d" % layout, flush=True)
+    dk.quantize_append(dc, t(new_len), bits(k), bits(v), t(score), quota=t(quota), total_new=n, max_new=n)
+    torch.cuda.synchronize()
+    assert int(dc.status.cpu()[0]) == 0
+    table, pool = dc.page_table.cpu().numpy()[0], dc.pool.cpu().numpy()
+    for sec in (0, 1):
+        T, kb, vb = Ld.tokens_per_page[sec], Ld.k_bits[sec], Ld.v_bits[sec]
+        page = pool[table[0] if sec == 0 else table[-1]]
+        chunks = kb  # 128 * kb / 128 chunks of 16 bytes per token
+        kc = codes_of(page[Ld.off_kcode[sec]:][:chunks * T * 16].reshape(chunks, T, 16), 128 // kb, kb)
+        kc = kc.transpose(1, 0, 2).reshape(T, 128)
+        vc = codes_of(page[Ld.off_vcode[sec]:][:128 * T * vb // 8].reshape(128, T * vb // 8), T, vb).T
+        km = page[Ld.off_kmeta[sec]:][:T * 16].view(np.float16).reshape(T, 4, 2)
+        vm = page[Ld.off_vmeta[sec]:][:T * 16].view(np.float16).reshape(4, T, 2)
+        for slot in range(half):
+            for g in range(4):
+                for x, b, code, meta in ((k, kb, kc, km[slot, g]), (v, vb, vc, vm[g, slot])):
+                    s, z, want = model_group(x[sec * half + slot, 0, g], b)
+                    assert np.array_equal(np.array([s, z]), meta, equal_nan=True), (sec, slot, g, s, z, meta)
+                    assert np.array_equal(code[slot, 32 * g:32 * g + 32], want), (sec, slot, g)
