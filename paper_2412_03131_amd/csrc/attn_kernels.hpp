@@ -1772,7 +1772,9 @@ __global__ __launch_bounds__(kSigWaves * kWave) void attn_significance(SigArgs a
     const auto* lenp = (const __attribute__((address_space(4))) int32_t*)(a.len + 2 * (long long)t);
     const int len_hi = lenp[0], len_lo = lenp[1];
     const int N = a.seq_len[b];
-    const int ph = (len_hi + LY::hi.T - 1) / LY::hi.T, np = ph + (len_lo + LY::lo.T - 1) / LY::lo.T;
+    // no length leads out of the table's row: its pages are at most its slots
+    const int ph = max((len_hi + LY::hi.T - 1) / LY::hi.T, 0);
+    const int np = min(ph + max((len_lo + LY::lo.T - 1) / LY::lo.T, 0), P);
     const int want = (np + kSigPages - 1) / kSigPages;
     const int nw = (want < a.shares ? want : a.shares) * kSigWaves, wv = share * kSigWaves + wave;
     if (wv >= nw) return;

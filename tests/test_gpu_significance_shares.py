@@ -3,10 +3,12 @@ grid gives them workgroups, with more than a workgroup's twelve (several workgro
 so many tables that each has one workgroup for a long table's pages."""
 import numpy as np
 import pytest
+import torch
 from test_gpu_significance import _compare, _step
 
-from gpu_util import dev_cache_from_oracle, layouts
+from gpu_util import dev_cache_from_oracle, layouts, t
 from oracle import oracle as orc
+from paper_2412_03131_amd import diffkv as dk
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +40,38 @@ def test_pages_dealt_to_workgroups(B, Hkv, gq, lens):
     print("case: significance pages dealt, B=%d" % B, flush=True)
     _step(dc, oc, q)
     assert _compare(dc, oc, "B=%d" % B) == rows * Hkv
+
+
+def test_lengths_past_the_table_stay_in_its_row():
+    """Section lengths of more pages than the table has slots: the row's own pages are read, nothing
+    past it (the neighbouring table's entries), and the neighbours' scores are as ever."""
+    rng = np.random.default_rng(3)
+    B, Hkv, gq = 3, 1, 2
+    new_len = np.array([40, 60, 90], np.int32)
+    rows = int(new_len.sum())
+    k = rng.standard_normal((rows, Hkv, 128)).astype(np.float16).view(np.uint16)
+    v = rng.standard_normal((rows, Hkv, 128)).astype(np.float16).view(np.uint16)
+    score = (rng.random((rows, Hkv)) * 0.01).astype(np.float32)
+    quota = np.zeros((B, Hkv, 2), np.int32)
+    quota[:, 0, 0] = new_len
+    Lo, Ld = layouts(max_seq_len=112)  # 8 slots per table
+    oc = orc.Cache(Lo, 32, B, Hkv, ring=rng.permutation(32))
+    orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+    dc = dev_cache_from_oracle(Ld, oc)
+    before = dc.pool.cpu().numpy().copy()
+    dc.len[0, 0] = 16 * 5000
+    q = rng.standard_normal((B, gq * Hkv, 128)).astype(np.float16).view(np.uint16)
+    lse = torch.full((B, gq * Hkv), 3.0, dtype=torch.float32, device="cuda")
+    print("case: significance, lengths past the table", flush=True)
+    dk.update_significance(dc, t(q), 1.0 / np.sqrt(128.0), lse)
+    torch.cuda.synchronize()
+    got = dc.pool.cpu().numpy()
+    # the same update of the neighbours alone, table 0 empty
+    dc.pool.copy_(torch.from_numpy(before))
+    dc.len[0] = 0
+    dk.update_significance(dc, t(q), 1.0 / np.sqrt(128.0), lse)
+    torch.cuda.synchronize()
+    want = dc.pool.cpu().numpy()
+    others = oc.table[1:][oc.table[1:] >= 0]
+    assert np.array_equal(got[others], want[others])
+    assert not np.array_equal(got[others], before[others])
