@@ -30,9 +30,9 @@ constexpr int kModePair = -2;  // launch mode of attn_pair (internal; never a ca
 constexpr int kPartStride = kD + 2;
 constexpr int kSigWaves = 4;
 // attn_significance: pages per working workgroup, and how many workgroups a call
-// launches at most (beyond one per table).  One workgroup per sixteen pages of the
-// longest table there can be was 17k workgroups for 512 tables of 72 pages, two
-// thirds of them with nothing to do.
+// launches (beyond one per table; up to twice that where tables can be long).  One
+// workgroup per sixteen pages of the longest table there can be was 17k workgroups for
+// 512 tables of 72 pages, five of 33 per table with work.
 constexpr int kSigPages = 12;
 constexpr int kSigGroups = 8192;
 

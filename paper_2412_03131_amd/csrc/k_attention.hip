@@ -112,7 +112,13 @@ hipError_t launch_significance(const SigArgs& args, hipStream_t st)
     const long long T = (long long)a.B * a.Hkv;
     if (T < 1) return hipErrorInvalidValue;
     const long long most = (a.p_max + kSigPages - 1) / kSigPages;
-    const long long shares = (kSigGroups + T - 1) / T;
+    // as many as keep the device busy; up to twice that while a wave could have more than
+    // eight pages of the longest table there can be (one sequence of 32k tokens among 63
+    // of 1k, 512 tables: 38.0 us with 16 per table, 30.0 with 32; 64 of 2k tokens with
+    // room for 32k: 18.3 and 19.7)
+    long long shares = (kSigGroups + T - 1) / T;
+    const long long deep = (a.p_max + 8 * kSigWaves - 1) / (8 * kSigWaves), room = 2 * kSigGroups / T;
+    if (deep > shares) shares = room < shares ? shares : (deep < room ? deep : room);
     a.shares = (int)(shares < most ? shares : most);
     const long long grid = T * a.shares;
     if (grid > INT32_MAX) return hipErrorInvalidValue;

@@ -75,3 +75,29 @@ def test_lengths_past_the_table_stay_in_its_row():
     others = oc.table[1:][oc.table[1:] >= 0]
     assert np.array_equal(got[others], want[others])
     assert not np.array_equal(got[others], before[others])
+
+
+@pytest.mark.parametrize("B,Hkv,gq,lens", [
+    (30, 8, 4, (9000, 300, 70)),   # 240 tables with room for 577 pages: between one and two times the usual
+    (70, 8, 1, (20000, 30)),       # 560 tables, one long: twice the usual
+])
+def test_long_tables_among_short_ones(B, Hkv, gq, lens):
+    rng = np.random.default_rng(B)
+    new_len = np.full(B, 5, np.int32)
+    new_len[:len(lens)] = lens
+    rows = int(new_len.sum())
+    k = (rng.standard_normal((rows, Hkv, 128)) * 2).astype(np.float16).view(np.uint16)
+    v = rng.standard_normal((rows, Hkv, 128)).astype(np.float16).view(np.uint16)
+    score = (rng.random((rows, Hkv)) * 0.01).astype(np.float32)
+    quota = np.zeros((B, Hkv, 2), np.int32)
+    quota[:, :, 0] = new_len[:, None] // 2
+    quota[:, :, 1] = new_len[:, None] - quota[:, :, 0]
+    Lo, Ld = layouts(max_seq_len=max(lens) + 200)
+    pages = int((-(-quota // 16)).sum()) + 64
+    oc = orc.Cache(Lo, pages, B, Hkv, ring=rng.permutation(pages))
+    orc.quantize_append(oc, new_len, k, v, score, quota=quota)
+    dc = dev_cache_from_oracle(Ld, oc)
+    q = rng.standard_normal((B, gq * Hkv, 128)).astype(np.float16).view(np.uint16)
+    print("case: significance, long among short, B=%d" % B, flush=True)
+    _step(dc, oc, q)
+    assert _compare(dc, oc, "B=%d" % B) == rows * Hkv
