@@ -1050,12 +1050,15 @@ __global__ __launch_bounds__(kCommitThreads) void append_one(AppendArgs a)
 // Allocation alone: alloc_plan (one workgroup) + alloc_write (wave per table)
 // ---------------------------------------------------------------------------
 // alloc_plan is a chain of one round of loads, one prefix sum and the stores, for as
-// many tables as a workgroup holds in registers (kAllocKeep per thread, tables in
-// thread order); it takes tables beyond those in further rounds, after a first
-// pass over all of them for the all-or-nothing verdict.  4096 tables: 7.6 us with
-// that pass and a 64-bit sum through shuffles for every size.
-constexpr int kAllocKeep = 8;
+// many tables as are quickest held in registers (kAllocKeep neighbouring ones per
+// thread).  Beyond those it makes a first pass over all tables for the all-or-nothing
+// verdict, then rounds of one table per thread: a thread's neighbouring tables are
+// strided accesses, and eight of them (8192 tables) took 16.5 us for the call where the
+// rounds take 11.  4096 tables: 8.4 us, 12 with the rounds and a 64-bit sum through
+// shuffles.
+constexpr int kAllocKeep = 4;
 
+template <bool KEEP>
 __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
 {
     const int tid = threadIdx.x;
@@ -1065,16 +1068,21 @@ __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
     const long long head = a.ring_ptr[0], tail = a.ring_ptr[1];
     auto demand = [&](int t) { return make_int2(a.demand[2 * t], a.demand[2 * t + 1]); };
     auto pages = [&](int t) { return make_int2(a.pages[2 * t], a.pages[2 * t + 1]); };
-    const bool kept = NT <= kAllocKeep * kPlanThreads;
-    const int per = kept ? (NT + kPlanThreads - 1) / kPlanThreads : kAllocKeep;
-    const int round = per * kPlanThreads;
     auto need = [](int2 d) { return (long long)(d.x > 0 ? d.x : 0) + (d.y > 0 ? d.y : 0); };
     auto check = [&](int2 d, int2 p) -> uint32_t {
         return (d.x < 0 || d.y < 0 ? (uint32_t)DIFFKV_ST_BAD_INPUT : 0u) |
                ((long long)p.x + p.y + d.x + d.y > a.p_max ? (uint32_t)DIFFKV_ST_TABLE_OVERFLOW : 0u);
     };
-    int2 d[kAllocKeep], p[kAllocKeep];
-    auto load = [&](int t0) {  // tables t0 .. of this thread (the last again past the end)
+    auto place = [&](int t, int2 d, int2 p, long long off) {
+        a.tstate[t] = make_int4(p.x, p.y, (int)off, d.x);
+        a.pages[2 * t] = p.x + d.x;
+        a.pages[2 * t + 1] = p.y + d.y;
+    };
+    long long sum = 0, total;
+    uint32_t flags = 0, bits = 0;
+    if constexpr (KEEP) {
+        const int per = (NT + kPlanThreads - 1) / kPlanThreads, t0 = tid * per;
+        int2 d[kAllocKeep], p[kAllocKeep];
 #pragma unroll
         for (int i = 0; i < kAllocKeep; ++i) {
             if (i >= per) break;  // (uniform)
@@ -1082,26 +1090,6 @@ __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
             d[i] = demand(t);
             p[i] = pages(t);
         }
-    };
-    long long sum = 0, total;
-    uint32_t flags = 0, bits = 0;
-    if (kept) {
-        load(tid * per);
-    } else {
-        for (int t = tid; t < NT; t += kPlanThreads) {
-            const int2 dt = demand(t);
-            flags |= check(dt, pages(t));
-            sum += need(dt);
-        }
-        block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits);
-        if (total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
-    }
-    long long carry = 0;
-    for (int r0 = 0; bits == 0 && r0 < NT; r0 += round) {
-        const int t0 = r0 + tid * per;
-        if (!kept) load(t0);
-        sum = 0;
-        flags = 0;
 #pragma unroll
         for (int i = 0; i < kAllocKeep; ++i) {
             if (i < per && t0 + i < NT) {
@@ -1109,19 +1097,33 @@ __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
                 flags |= check(d[i], p[i]);
             }
         }
-        long long off = block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits) + carry;
-        if (kept && total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
-        if (bits) break;
-        carry += total;
+        long long off = block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits);
+        if (total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
+        if (!bits) {
 #pragma unroll
-        for (int i = 0; i < kAllocKeep; ++i) {
-            if (i < per && t0 + i < NT) {
-                const int t = t0 + i;
-                a.tstate[t] = make_int4(p[i].x, p[i].y, (int)off, d[i].x);
-                a.pages[2 * t] = p[i].x + d[i].x;
-                a.pages[2 * t + 1] = p[i].y + d[i].y;
-                off += d[i].x + d[i].y;
+            for (int i = 0; i < kAllocKeep; ++i) {
+                if (i < per && t0 + i < NT) {
+                    place(t0 + i, d[i], p[i], off);
+                    off += d[i].x + d[i].y;
+                }
             }
+        }
+    } else {
+        for (int t = tid; t < NT; t += kPlanThreads) {
+            const int2 d = demand(t);
+            flags |= check(d, pages(t));
+            sum += need(d);
+        }
+        block_excl_scan_wide(sum, s_scan, &total, flags, s_bits, &bits);
+        if (total > tail - head) bits |= DIFFKV_ST_OUT_OF_PAGES;
+        long long carry = 0;
+        for (int t0 = 0; bits == 0 && t0 < NT; t0 += kPlanThreads) {
+            const int t = t0 + tid;
+            const int2 d = t < NT ? demand(t) : make_int2(0, 0);
+            int all;  // (a round's pages: at most the ring's, which a 32-bit number counts)
+            const int off = block_excl_scan<int>(d.x + d.y, reinterpret_cast<int*>(s_scan), &all);
+            if (t < NT) place(t, d, pages(t), carry + off);
+            carry += all;
         }
     }
     if (tid == 0) {
@@ -1131,7 +1133,7 @@ __global__ __launch_bounds__(kPlanThreads) void alloc_plan(AllocArgs a)
         } else {
             a.flags->head_old = head;
             a.flags->ok = 1;
-            a.ring_ptr[0] = head + carry;
+            a.ring_ptr[0] = head + total;
         }
     }
 }
@@ -1383,7 +1385,8 @@ hipError_t launch_append(const AppendArgs& args, int grid_quant, hipStream_t st)
 
 hipError_t launch_alloc(const AllocArgs& a, hipStream_t st)
 {
-    hipError_t e = launch1(alloc_plan, 1, kPlanThreads, st, a);
+    hipError_t e = launch1(a.num_tables <= kAllocKeep * kPlanThreads ? alloc_plan<true> : alloc_plan<false>, 1, kPlanThreads,
+                           st, a);
     if (e != hipSuccess || a.num_tables == 0) return e;
     return launch1(alloc_write, (unsigned)a.num_tables, kWave, st, a);
 }

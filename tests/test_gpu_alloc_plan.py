@@ -1,5 +1,5 @@
-"""The allocation plan over the table counts where it changes: one thread's tables, one
-round kept in registers (8192 tables), several rounds; and its refusals."""
+"""The allocation plan over the table counts where it changes: one thread's tables, all of
+them kept in registers (4096 tables), rounds of 1024; and its refusals."""
 import numpy as np
 import pytest
 from gpu_util import assert_state_equal, dev_cache_from_oracle, layouts, t
@@ -10,7 +10,7 @@ from paper_2412_03131_amd import diffkv as dk
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("tables", [1, 1023, 1025, 8192, 8193, 20000])
+@pytest.mark.parametrize("tables", [1, 1023, 1025, 4096, 4097, 8192, 8193, 20000])
 def test_alloc_plan(tables):
     rng = np.random.default_rng(tables)
     Lo, Ld = layouts(max_seq_len=240)  # 16 slots per table
