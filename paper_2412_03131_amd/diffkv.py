@@ -65,7 +65,7 @@ def lib():
         L = C.CDLL(LIB_PATH)
         vp, i32, i64, f32, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_size_t
         PL = C.POINTER(Layout)
-        PC = vp  # a CacheStruct by reference, or its packed bytes (_cache_bytes)
+        PC = C.POINTER(CacheStruct)
         L.diffkv_layout_init.argtypes = [PL, i32, i32, vp, vp, vp, i32]
         L.diffkv_workspace_size.argtypes = [i32, PL, i32, i32, i32, i64, i32, C.POINTER(sz)]
         L.diffkv_quantize_append.argtypes = [PL, PC, i64, i32, vp, vp, vp, vp, vp, f32, f32, i32,
@@ -125,16 +125,17 @@ def workspace_size(op, L, num_seqs, num_q_heads=0, num_kv_heads=1, total_new=0, 
 
 # The calls below cost the host what a short kernel costs the device, so what they
 # marshal is kept to the call's own arguments: the cache's addresses packed into
-# bytes, the stream's address, plain integers, and no size query for a workspace
-# that the caller brings (the library checks its size).
+# the structure at once, the stream's address, plain integers, and no size query for
+# a workspace that the caller brings (the library checks its size).
 _CACHE = struct.Struct("PqPPPPPPPii")
 assert _CACHE.size == C.sizeof(CacheStruct)
 
 
-def _cache_bytes(c):
-    return _CACHE.pack(c.pool.data_ptr(), c.num_pages, c.page_table.data_ptr(), c.pages.data_ptr(),
-                       c.len.data_ptr(), c.seq_len.data_ptr(), c.ring.data_ptr(), c.ring_ptr.data_ptr(),
-                       c.status.data_ptr(), c.num_seqs, c.num_kv_heads)
+def _cache_struct(c):
+    return CacheStruct.from_buffer_copy(_CACHE.pack(
+        c.pool.data_ptr(), c.num_pages, c.page_table.data_ptr(), c.pages.data_ptr(), c.len.data_ptr(),
+        c.seq_len.data_ptr(), c.ring.data_ptr(), c.ring_ptr.data_ptr(), c.status.data_ptr(), c.num_seqs,
+        c.num_kv_heads))
 
 
 def _new_ws(nbytes, device):
@@ -218,7 +219,7 @@ def quantize_append(cache, new_len, k, v, score, quota=None, alpha_h=0.0, alpha_
     if ws is None:
         ws = _new_ws(workspace_size(*sizes), cache.pool.device)
     _check_ws(lib().diffkv_quantize_append(
-        C.byref(L), _cache_bytes(cache), int(total_new), int(max_new), _ptr(new_len), _ptr(_bits16(k)),
+        C.byref(L), _cache_struct(cache), int(total_new), int(max_new), _ptr(new_len), _ptr(_bits16(k)),
         _ptr(_bits16(v)), _ptr(score), _ptr(quota), float(alpha_h), float(alpha_l), int(window),
         ws.data_ptr(), ws.nbytes, _stream(stream)), "diffkv_quantize_append", *sizes)
     return ws
@@ -237,7 +238,7 @@ def decode_attention(cache, q, sm_scale, out=None, lse=None, num_splits=0, ws=No
     if ws is None:
         ws = _new_ws(workspace_size(*sizes), q.device)
     _check_ws(lib().diffkv_decode_attention(
-        C.byref(L), _cache_bytes(cache), Hq, _ptr(_bits16(q)), float(sm_scale), _ptr(out), _ptr(lse),
+        C.byref(L), _cache_struct(cache), Hq, _ptr(_bits16(q)), float(sm_scale), _ptr(out), _ptr(lse),
         int(num_splits), ws.data_ptr(), ws.nbytes, _stream(stream)), "diffkv_decode_attention", *sizes)
     return out, lse
 
@@ -246,7 +247,7 @@ def decode_attention_noalloc(cache, q, sm_scale, out, lse=None, num_splits=0, st
     """diffkv_decode_attention_noalloc: like decode_attention, outputs given by the
     caller, no workspace (the library's fixed per-device scratch)."""
     _check(lib().diffkv_decode_attention_noalloc(
-        C.byref(cache.L), _cache_bytes(cache), q.shape[1], _ptr(_bits16(q)), float(sm_scale), _ptr(out),
+        C.byref(cache.L), _cache_struct(cache), q.shape[1], _ptr(_bits16(q)), float(sm_scale), _ptr(out),
         _ptr(lse), int(num_splits), _stream(stream)), "diffkv_decode_attention_noalloc")
     return out, lse
 
@@ -255,7 +256,7 @@ def update_significance(cache, q, sm_scale, lse, stream=None):
     """diffkv_update_significance: every kept token's score becomes the running mean of
     its attention probability (max over the KV head's query heads); lse from
     decode_attention with the same q."""
-    _check(lib().diffkv_update_significance(C.byref(cache.L), _cache_bytes(cache), q.shape[1], _ptr(_bits16(q)),
+    _check(lib().diffkv_update_significance(C.byref(cache.L), _cache_struct(cache), q.shape[1], _ptr(_bits16(q)),
                                             float(sm_scale), _ptr(lse), _stream(stream)),
            "diffkv_update_significance")
 
@@ -288,7 +289,7 @@ def compact_free_list(cache, release, num_tables=None, ws=None, stream=None):
     sizes = (OP_COMPACT, L, cache.num_seqs, 0, cache.num_kv_heads)
     if ws is None:
         ws = _new_ws(workspace_size(*sizes), cache.pool.device)
-    _check_ws(lib().diffkv_compact_free_list(C.byref(L), _cache_bytes(cache), int(nt), _ptr(release), ws.data_ptr(), ws.nbytes,
+    _check_ws(lib().diffkv_compact_free_list(C.byref(L), _cache_struct(cache), int(nt), _ptr(release), ws.data_ptr(), ws.nbytes,
                        _stream(stream)), "diffkv_compact_free_list", *sizes)
     return ws
 
@@ -300,7 +301,7 @@ def alloc_pages(cache, demand, num_tables=None, ws=None, stream=None):
     sizes = (OP_ALLOC, L, cache.num_seqs, 0, cache.num_kv_heads)
     if ws is None:
         ws = _new_ws(workspace_size(*sizes), cache.pool.device)
-    _check_ws(lib().diffkv_alloc_pages(C.byref(L), _cache_bytes(cache), int(nt), _ptr(demand), ws.data_ptr(), ws.nbytes,
+    _check_ws(lib().diffkv_alloc_pages(C.byref(L), _cache_struct(cache), int(nt), _ptr(demand), ws.data_ptr(), ws.nbytes,
                        _stream(stream)), "diffkv_alloc_pages", *sizes)
     return ws
 
@@ -311,7 +312,7 @@ def generation_step(cache, alpha_h, alpha_l, recent_window, ws=None, stream=None
     sizes = (OP_GENERATION, L, cache.num_seqs, 0, cache.num_kv_heads)
     if ws is None:
         ws = _new_ws(workspace_size(*sizes), cache.pool.device)
-    _check_ws(lib().diffkv_generation_step(C.byref(L), _cache_bytes(cache), float(alpha_h), float(alpha_l),
+    _check_ws(lib().diffkv_generation_step(C.byref(L), _cache_struct(cache), float(alpha_h), float(alpha_l),
                                            int(recent_window), ws.data_ptr(), ws.nbytes, _stream(stream)),
               "diffkv_generation_step", *sizes)
     return ws

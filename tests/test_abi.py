@@ -79,6 +79,18 @@ def test_workspace_sizes(dk):
     assert dk.workspace_size(dk.OP_GENERATION, L, 64, 0, 8) >= 512 * (16 + 16 + 4 + 4)
 
 
+def test_cache_argument_is_typed(dk):
+    """The cache goes to the library as a CacheStruct, by reference or not, and nothing else does."""
+    lib = dk.lib()
+    L = dk.layout(max_seq_len=64)
+    st = dk.CacheStruct(0, 16, 0, 0, 0, 0, 0, 0, 0, 2, 2)
+    for arg in (st, C.byref(st), C.pointer(st)):
+        assert lib.diffkv_update_significance(C.byref(L), arg, 4, None, 0.1, None, None) == dk.E_INVAL
+    for arg in (C.byref(L), L, bytes(C.sizeof(st)), 0x1000):
+        with pytest.raises(C.ArgumentError):
+            lib.diffkv_update_significance(C.byref(L), arg, 4, None, 0.1, None, None)
+
+
 def test_argument_checks_enqueue_nothing(dk):
     """Invalid calls return before touching the device (NULL pointers, bad shapes)."""
     lib = dk.lib()
