@@ -205,11 +205,23 @@ constexpr int kPromptCtrStride = 32;
 // blocks than would keep the device busy, each block's queries are cut, down to
 // eight ways (the first block of one 4999-token prompt holds an eightieth of the
 // work of its 160 blocks, so the pass took as long as that one block: 867 us at 64
-// query heads, 241 us cut).  A sum over segments replaces the direct store.
+// query heads, 210 us cut).  A sum over segments replaces the direct store.  The numbers
+// of blocks are for a device of 256 CUs, two workgroups each.
 constexpr int kPromptBusyBlocks = 2048;
 constexpr int kPromptMaxSegs = 8;
 constexpr int kPromptFewStagesBlocks = 512;
-// No more than the longest prompt has stages of query positions (128 at one query head
+
+// Most values the segments' sums take for any number of KV heads (Hq / 8 .. Hq):
+// the workspace size is not told it.
+inline long long prompt_part_rows(long long B, long long Hq, long long total_new)
+{
+    const long long per_head = total_new / 256 + B;
+    if (per_head <= 0 || per_head * ((Hq + 7) / 8) >= kPromptBusyBlocks) return 0;
+    const long long cut = kPromptBusyBlocks / per_head + 1 + Hq, all = kPromptMaxSegs * Hq;
+    return total_new * (cut < all ? cut : all);
+}
+
+// No more segments than the longest prompt has stages of query positions (128 at one query head
 // per KV head, 64 at two, else 32), and for prompts of a few stages only as many as
 // run at once: a stage is then worth less than the launch that adds the segments (256
 // prompts of 100 tokens, 4 / 1 heads: 21.0 us in four segments, 17.6 whole).
@@ -222,16 +234,10 @@ inline int prompt_segs(long long B, long long Hq, long long Hkv, long long total
     const long long g = Hq / Hkv, stage = g == 1 ? 128 : (g == 2 ? 64 : 32), stages = (max_new + stage - 1) / stage;
     if (s > stages) s = stages;
     if (stages <= kPromptMaxSegs && s > kPromptFewStagesBlocks / blocks) s = kPromptFewStagesBlocks / blocks;
+    // (never more than the workspace holds, whatever the constants above)
+    const long long room = total_new > 0 ? prompt_part_rows(B, Hq, total_new) / (total_new * Hkv) : 1;
+    if (s > room) s = room;
     return (int)(s < 1 ? 1 : s);
-}
-// Most values the segments' sums take for any number of KV heads (Hq / 8 .. Hq):
-// the workspace size is not told it.
-inline long long prompt_part_rows(long long B, long long Hq, long long total_new)
-{
-    const long long per_head = total_new / 256 + B;
-    if (per_head <= 0 || per_head * ((Hq + 7) / 8) >= kPromptBusyBlocks) return 0;
-    const long long cut = kPromptBusyBlocks / per_head + 1 + Hq, all = kPromptMaxSegs * Hq;
-    return total_new * (cut < all ? cut : all);
 }
 hipError_t launch_prompt_significance(const PromptArgs& a, int g, hipStream_t st);
 
