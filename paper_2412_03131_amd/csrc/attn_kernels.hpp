@@ -1412,24 +1412,30 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
 // of the concatenated list gives a table 64 shares of a page or none, whose
 // arrivals and merge were the whole call (190 us; 9.5 now).  Shares that cross a
 // table boundary also cost a second segment start and a second arrival.  So every
-// table is cut into ceil(p / kOwnUnits) equal ranges of its p page units, one
-// workgroup each, a table in one range having no merge, wherever these ranges fit
-// the W resident workgroups.  kOwnUnits is a high page for every wave: the longest
-// chain of v_dot2 sums in a wave is then one page, the shortest there is, whatever
-// the cut list's would be.  Longer ranges would be faster (one sequence of 8000 and
-// 32768 tokens at GQ 4: 13.3 and 18.8 us with 2 sqrt(p) units, 15.7 and 24.7 now, 117
-// and 111 cut; 16 sequences of 2000 tokens, 128 tables: 16.1 with 98 units, 19.2 cut),
-// but a wave's weights are fp16 relative to the largest of its chain, so the
-// error against 64 bits grows with the chain: up to 1.39 times the cut list's where
-// the ranges were as long as it took to fit W workgroups, the same (1.00) here.
+// table is cut into ceil(p / quantum) equal ranges of its p page units, one workgroup
+// each, a table in one range having no merge, wherever these ranges fit the W resident
+// workgroups with a quantum of
+//   kOwnUnits          a high page for every wave: the longest chain of v_dot2 sums in a
+//                      wave is then one page, the shortest there is, whatever the cut
+//                      list's would be;
+//   sum of p / (W - T) for tables that are few beside W (kOwnFew): the ranges are then
+//                      about as long as the cut list's W + T pieces.
+// Longer ranges would be faster (one sequence of 8000 and 32768 tokens at GQ 4: 13.3
+// and 18.8 us with 2 sqrt(p) units, 15.7 and 24.7 now, 117 and 111 cut; 16 sequences of 2000
+// tokens, 128 tables: 16.1 with 98 units, 19.5 cut; 5 of 1000 to 6000 at GQ 7, 20 tables:
+// 16.5 with 43, 23.6 cut), but a wave's weights are fp16 relative to the largest of its
+// chain, so the error against 64 bits grows with the chain.  With ranges as long as it
+// takes to fit W workgroups it is 0.99 times the cut list's for T up to W / 32 (60
+// calls, geometric mean), 1.04 from there to W / 16 and up to 1.39 above.
 template <int LI, int NW>
 constexpr int kOwnUnits = NW * Units<LI>::hi;
+constexpr int kOwnFew = 32;
 
 // Ranges of a table of `units` units (0: empty).
-template <int LI, int NW>
-__device__ __forceinline__ int own_ranges(long long units)
+template <int LI>
+__device__ __forceinline__ int own_ranges(long long units, int quantum)
 {
-    return units > 0 ? ((int)units - Units<LI>::seg + kOwnUnits<LI, NW> - 1) / kOwnUnits<LI, NW> : 0;
+    return units > 0 ? ((int)units - Units<LI>::seg + quantum - 1) / quantum : 0;
 }
 
 template <int GQ, int LI>
@@ -1472,9 +1478,13 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
     const int t1 = t0 + per < T ? t0 + per : T;
     long long units[kKeep];
     long long mine = 0;
-    // thread 0 of workgroup t reads the arrival word of table t, for the claim below
+    // Thread 0 of workgroup t claims the arrival word of table t for this call (the shares
+    // of a split table arrive together: without the claim each retries a compare-and-swap
+    // against the others, 2 us per share; four sequences of 12000 tokens at GQ 4 24.8 and
+    // 31.7 us).  It reads the word after the lengths: their wait is then not the word's,
+    // which comes from farther (0.5 us of a 20 us call).
     const bool claim = threadIdx.x == 0 && k < T;
-    const unsigned long long word = claim ? arrive_peek(a.arrive + k) : 0ull;
+    unsigned long long word = 0;
     {
         // all loads first (clamped to a valid table), then the units
         int lh[kKeep], ll[kKeep];
@@ -1484,6 +1494,7 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
             lh[i] = a.len[2 * tc];
             ll[i] = a.len[2 * tc + 1];
         }
+        if (claim) word = arrive_peek(a.arrive + k);
 #pragma unroll
         for (int i = 0; i < kKeep; ++i) {
             units[i] = t0 + i < t1 ? table_info_of<LI>(a, lh[i], ll[i]).units : 0;
@@ -1505,22 +1516,34 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
     }
     long long b_lo, b_hi;
     // (the ranges hold all page units, so more than W * kOwnUnits of these never fit)
-    int own = 0, at = 0;
-    if (T <= W && total <= W * kOwnUnits<LI, NW> + (long long)T * Units<LI>::seg) {
-        int cnt = 0;
-        for (int t = t0; t < t1; ++t) cnt += own_ranges<LI, NW>(t == t0 ? units[0] : table_info<LI>(a, t).units);
-        at = block_excl_scan<int>(cnt, reinterpret_cast<int*>(sh.scan), &own);
+    int own = 0, at = 0, quantum = kOwnUnits<LI, NW>;
+    const bool few = T * kOwnFew <= W && total * T <= Units<LI>::seg * W * (W - T);
+    if (few || (T <= W && total <= W * quantum + (long long)T * Units<LI>::seg)) {
+        int held = 0;  // tables with pages
+        auto count = [&]() {
+            long long cnt = 0, all;  // ranges, and tables with pages in the upper half
+            for (int t = t0; t < t1; ++t) {
+                const int n = own_ranges<LI>(t == t0 ? units[0] : table_info<LI>(a, t).units, quantum);
+                cnt += n | (long long)(n > 0) << 32;
+            }
+            at = (int)block_excl_scan<long long>(cnt, sh.scan, &all);
+            own = (int)all;
+            held = (int)(all >> 32);
+        };
+        count();
+        if (few && own > W) {
+            const int pages = (int)(total - (long long)held * Units<LI>::seg), room = (int)W - held;
+            quantum = (pages + room - 1) / room;
+            count();
+        }
     }
+    if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
     if (own <= W && own > 0) {
-        // The shares of a split table arrive together here: without the claim each
-        // retries a compare-and-swap against the others, 2 us per share.  (The cut
-        // list's arrive apart: the claim changed nothing there.)
-        if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
         if (k >= own) return;
         long long u = before;
         for (int t = t0; t < t1; ++t) {
             const long long un = t == t0 ? units[0] : table_info<LI>(a, t).units;
-            const int n = own_ranges<LI, NW>(un);
+            const int n = own_ranges<LI>(un, quantum);
             if (at <= k && k < at + n) {
                 const int c = (int)k - at, pu = (int)un - Units<LI>::seg;
                 sh.t_first = t;

@@ -27,41 +27,53 @@ def page_at_unit(x, ph, np_):
     return min(p, np_)
 
 
-def own_ranges(ph, pl, waves):
+def quantum_of(tabs, T, W, waves):
+    """The range length of tables [(ph, pl)], or None where the list is cut."""
+    pus = [HI * a + LO * b for a, b in tabs if a + b]
+    total = sum(pus) + SEG * len(pus)
+    few = 32 * T <= W and total * T <= SEG * W * (W - T)
+    q = waves * HI
+    if not few and (T > W or total > W * q + T * SEG):
+        return None
+    if few and sum(-(-p // q) for p in pus) > W:
+        q = -(-sum(pus) // (W - len(pus)))
+    return q if 0 < sum(-(-p // q) for p in pus) <= W else None
+
+
+def ranges_of(ph, pl, quantum):
     pu = HI * ph + LO * pl
-    return -(-pu // (waves * HI))
-
-
-def ranges_of(ph, pl, waves):
-    pu, n = HI * ph + LO * pl, own_ranges(ph, pl, waves)
+    n = -(-pu // quantum)
     cut = [0] + [SEG + c * pu // n for c in range(1, n + 1)]
     return [(page_at_unit(cut[c], ph, ph + pl), page_at_unit(cut[c + 1], ph, ph + pl)) for c in range(n)]
 
 
 def test_own_shares_cover_every_page_once():
-    """Every page lies in one range, the ranges fit the workgroups, and no range holds more
-    than one page per wave (the length of a wave's chain, on which the error depends)."""
+    """Every page lies in one range, and no range holds more than one page per wave (the length of a
+    wave's chain, on which the error depends), or, with few tables, is longer than the shares of
+    the cut list by more than their number falls behind its W + T pieces."""
     rng = random.Random(5)
-    checked = 0
-    for _ in range(4000):
+    checked = longer = 0
+    for _ in range(6000):
         W, waves = rng.choice(((512, 8), (256, 12)))
         T = int(math.exp(rng.uniform(0, math.log(W))))
         top = int(math.exp(rng.uniform(0, math.log(3000))))
         tabs = [(rng.randint(0, top), rng.randint(0, top)) for _ in range(T)]
-        used = sum(own_ranges(a, b, waves) for a, b in tabs)
-        total = sum(SEG + HI * a + LO * b for a, b in tabs if a + b)
-        if used > W:
+        q = quantum_of(tabs, T, W, waves)
+        if q is None:
             continue
-        assert total <= W * waves * HI + T * SEG  # the kernel's test before it counts the ranges
         checked += 1
+        total = sum(SEG + HI * a + LO * b for a, b in tabs if a + b)
+        if q > waves * HI:
+            longer += 1
+            assert 32 * T <= W and q <= total / W * (W / (W - T)) + 1
         for a, b in tabs:
             if a + b == 0:
                 continue
-            r = ranges_of(a, b, waves)
+            r = ranges_of(a, b, q)
             assert r[0][0] == 0 and r[-1][1] == a + b
-            assert all(x[1] == y[0] for x, y in zip(r, r[1:]))
-            assert all(0 < x[1] - x[0] <= waves for x in r)
-    assert checked > 500
+            assert all(x[1] == y[0] and x[0] < x[1] for x, y in zip(r, r[1:]))
+            assert q > waves * HI or all(0 < x[1] - x[0] <= waves for x in r)
+    assert checked > 500 and longer > 100
 
 
 def claim_once(w, tag):
@@ -102,6 +114,8 @@ def test_one_attempt_claim_loses_no_arrival():
     (3, 1, 8, 0, (2600, 300, 0)),               # twelve waves, an empty table
     (5, 1, 7, 1, (33, 500, 1100, 1700, 2300)),  # one to eight ranges, 8-bit values
     (4, 2, 3, 2, (1900, 900, 450, 60)),
+    (2, 4, 8, 0, (9000, 7000)),                 # few tables, ranges longer than a page per wave
+    (2, 4, 6, 3, (6000, 0)),                    # the same with empty tables
 ])
 def test_own_shares_match_oracle(B, Hkv, gq, layout, lens):
     import torch
