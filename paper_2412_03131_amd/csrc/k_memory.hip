@@ -2,10 +2,10 @@
 // kernels for gfx950 (DiffKV Sec. 4, Sec. 5.2, Sec. 5.3).
 //
 // The compressor runs as two launches on the caller's stream:
-//   append_classify  one workgroup per table: classes its new tokens (quota
-//                    form by a two-target radix select on the score bits, or
-//                    the Algorithm 1 threshold comparisons), ranks the kept
-//                    tokens of each section in position order;
+//   append_classify  one or more workgroups per table: class its new tokens
+//                    (quota form by a two-target radix select on the score
+//                    bits, or the Algorithm 1 threshold comparisons) and rank
+//                    the kept tokens of each section in position order;
 //   append_commit    every workgroup derives the plan from the classify
 //                    results (page demand per table, one prefix sum over
 //                    tables, all-or-nothing check against the free region and
@@ -56,7 +56,7 @@ static_assert(4 * kClsPer <= 32, "a thread keeps four flag bits per token of a t
 constexpr int kClsTile = kClsThreads * kClsPer;  // the first tile's scores stay in registers
 constexpr int kClsWaves = kClsThreads / kWave;
 static_assert(kClsPer * kClsWaves == kWave, "a wave scans a tile's counts");
-constexpr int kClsBusyGroups = 512;  // workgroups that keep the device busy (two per CU)
+constexpr int kClsBusyGroups = 512;  // workgroups that keep the device busy (two per CU of 256)
 static_assert(kClsTile < 65536, "16-bit counts");
 constexpr uint32_t kOffSat = 1u << 30;           // row offsets saturate here (above any total_new)
 
@@ -360,7 +360,7 @@ constexpr int kPlanThreads = 1024;
 // ---------------------------------------------------------------------------
 constexpr int kQuantWaves = kAppendJobsPerGroup;  // page jobs a workgroup runs side by side, one per wave
 constexpr int kCommitThreads = kQuantWaves * kWave;
-constexpr int kCommitWaves = 4;  // waves per SIMD of the bulk commit: 3 measured 194, 4 169, 5 (spills) 183 us
+constexpr int kCommitWaves = 4;  // waves per SIMD; whole prefills of 64 prompts of 1k-4k tokens: 3 171, 4 171, 5 (spills) 188 us
 
 struct TablePlan {
     int need[2], jobs[2];
@@ -1368,7 +1368,8 @@ hipError_t launch_append(const AppendArgs& args, int grid_quant, hipStream_t st)
 {
     AppendArgs a = args;
     if (append_one_call(a)) return launch1(append_one, (unsigned)(a.Hkv * a.B), kCommitThreads, st, a);
-    // a table's tiles go to several workgroups while there are fewer tables than CUs
+    // a table's tiles go to several workgroups while all of these stay within kClsBusyGroups
+    // (up to half as many tables)
     const int tables = a.Hkv * a.B, tiles = (int)(((long long)a.max_new + kClsTile - 1) / kClsTile);
     const int room = kClsBusyGroups / tables;
     a.cls_split = tiles < room ? tiles : room;

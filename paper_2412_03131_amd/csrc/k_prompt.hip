@@ -595,7 +595,7 @@ namespace {
 unsigned pass_grid(long long items, int max_new, int most, int cus, int per_cu, int* once)
 {
     const long long resident = (long long)cus * per_cu;
-    *once = items <= most * resident || max_new <= 512;
+    *once = items <= most * resident || (max_new <= 512 && items <= 1 << 22);  // (a launch's threads fit 32 bits)
     return (unsigned)(*once ? items : resident);
 }
 
