@@ -82,13 +82,17 @@ struct Cuts {
     int need[2];
 };
 
+// PER: tokens per thread in one tile: kClsPer, or one where no sequence has more tokens than
+// the workgroup threads (8 tokens to 128 tables: 14.6 -> 14.0 us for the call).
+template <int PER>
 __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
 {
+    constexpr int kTile = kClsThreads * PER;
     const int H = a.Hkv, NT = a.B * H;
     const int split = blockIdx.x / NT, t = blockIdx.x - split * NT;
     const int b = t / H, h = t - b * H;
     const int tid = threadIdx.x;
-    __shared__ long long s_cnt[2][kClsPer * kClsWaves];  // a tile's class counts by step and wave, in position order
+    __shared__ long long s_cnt[2][PER * kClsWaves];  // a tile's class counts by step and wave, in position order
     __shared__ int s_before[4];                          // class counts of the tiles before this workgroup's
     __shared__ int s_hist[2][2][256];  // [buffer][cut][digit]
     __shared__ int s_sel[4];
@@ -138,7 +142,7 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
         return;
     }
     // this workgroup's tiles [c0, c1) of the table's
-    const int tiles = n > kClsTile ? (n + kClsTile - 1) / kClsTile : 1;
+    const int tiles = n > kTile ? (n + kTile - 1) / kTile : 1;
     const int per = (tiles + a.cls_split - 1) / a.cls_split;
     const int c0 = split * per, c1 = c0 + per < tiles ? c0 + per : tiles;
     if (c0 >= tiles) return;
@@ -151,15 +155,15 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     const float* sc = a.score + off_b * H + h;
     int32_t* ord = a.ord + off_b * H + (long long)h * n;
 
-    // scores of step i .. of a tile from `base` on, kClsPer steps' loads together
-    auto load_scores = [&](int base, float (&v)[kClsPer]) {
+    // scores of step i .. of a tile from `base` on, PER steps' loads together
+    auto load_scores = [&](int base, float (&v)[PER]) {
 #pragma unroll
-        for (int i = 0; i < kClsPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const int j = base + i * kClsThreads + tid;
             v[i] = j < avail ? sc[(long long)j * H] : 0.f;
         }
     };
-    float sr[kClsPer];  // the first tile's stay in registers
+    float sr[PER];  // the first tile's stay in registers
     load_scores(0, sr);
 
     Cuts c = {{0, 0}, {0, 0}, {0, 0}};
@@ -175,16 +179,16 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
             // from the top; histograms double-buffered so each digit costs two barriers
             uint32_t prefix[2] = {0, 0}, mask = 0;
             int kk[2] = {c.mode[0] == 2 ? cut[0] : 0, c.mode[1] == 2 ? cut[1] : 0};
-            uint32_t kr[kClsPer];
+            uint32_t kr[PER];
 #pragma unroll
-            for (int i = 0; i < kClsPer; ++i) kr[i] = score_key(sr[i]);
+            for (int i = 0; i < PER; ++i) kr[i] = score_key(sr[i]);
 #pragma unroll
             for (int pass = 0; pass < 4; ++pass) {
                 const int shift = 24 - 8 * pass;
                 int* hist = &s_hist[pass & 1][0][0];
-                auto digits = [&](int base, const uint32_t (&k8)[kClsPer]) {
+                auto digits = [&](int base, const uint32_t (&k8)[PER]) {
 #pragma unroll
-                    for (int i = 0; i < kClsPer; ++i) {
+                    for (int i = 0; i < PER; ++i) {
                         if (base + i * kClsThreads + tid < avail) {
                             const uint32_t key = k8[i];
                             const uint32_t dig = (key >> shift) & 255u;
@@ -195,12 +199,12 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
                     }
                 };
                 digits(0, kr);
-                for (int base = kClsTile; base < avail; base += kClsTile) {  // beyond the first tile
-                    float v[kClsPer];
+                for (int base = kTile; base < avail; base += kTile) {  // beyond the first tile
+                    float v[PER];
                     load_scores(base, v);
-                    uint32_t k8[kClsPer];
+                    uint32_t k8[PER];
 #pragma unroll
-                    for (int i = 0; i < kClsPer; ++i) k8[i] = score_key(v[i]);
+                    for (int i = 0; i < PER; ++i) k8[i] = score_key(v[i]);
                     digits(base, k8);
                 }
                 for (int i = tid; i < 512; i += kClsThreads) (&s_hist[(pass + 1) & 1][0][0])[i] = 0;  // the next digit's buffer
@@ -276,11 +280,11 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
     int c_f[4] = {0, 0, 0, 0};  // counts before the tile
     if (c0 > 0) {
         int mine[4] = {0, 0, 0, 0};  // (uniform) this wave's
-        for (int base = 0; base < c0 * kClsTile; base += kClsTile) {
-            float v[kClsPer];
+        for (int base = 0; base < c0 * kTile; base += kTile) {
+            float v[PER];
             load_scores(base, v);
 #pragma unroll
-            for (int i = 0; i < kClsPer; ++i) {
+            for (int i = 0; i < PER; ++i) {
                 const uint32_t f = flags_of(base + i * kClsThreads + tid, v[i]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) mine[q] += __popcll(__builtin_amdgcn_ballot_w64(f >> q & 1u));
@@ -292,19 +296,19 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
         for (int q = 0; q < 4; ++q) c_f[q] = s_before[q];
     }
     for (int ct = c0; ct < c1; ++ct) {
-        const int base = ct * kClsTile;
-        float v[kClsPer];
+        const int base = ct * kTile;
+        float v[PER];
         if (ct > 0) {
             load_scores(base, v);
         } else {
 #pragma unroll
-            for (int i = 0; i < kClsPer; ++i) v[i] = sr[i];
+            for (int i = 0; i < PER; ++i) v[i] = sr[i];
         }
         // per step and wave the four counts, 16 bits each (a tile has 4096 tokens)
         uint32_t fl = 0;  // four flag bits per token
         long long* cnt = s_cnt[ct & 1];
 #pragma unroll
-        for (int i = 0; i < kClsPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const uint32_t f = flags_of(base + i * kClsThreads + tid, v[i]);
             fl |= f << (4 * i);
             long long p = 0;
@@ -313,11 +317,11 @@ __global__ __launch_bounds__(kClsThreads) void append_classify(AppendArgs a)
             if (lane == 0) cnt[i * kClsWaves + wave] = p;
         }
         __syncthreads();  // (the other buffer is free again: every wave has passed its last barrier's reads)
-        const long long own = cnt[lane];
+        const long long own = lane < PER * kClsWaves ? cnt[lane] : 0;
         const long long incl = wave_incl_scan64(own), excl = incl - own;  // (no carry between the 16-bit fields)
         const long long tot = read_lane<long long>(incl, kWave - 1);
 #pragma unroll
-        for (int i = 0; i < kClsPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             if (base + i * kClsThreads >= n) break;  // (uniform)
             const uint32_t f = fl >> (4 * i);
             const long long ex = read_lane<long long>(excl, i * kClsWaves + wave);
@@ -361,6 +365,15 @@ constexpr int kPlanThreads = 1024;
 constexpr int kQuantWaves = kAppendJobsPerGroup;  // page jobs a workgroup runs side by side, one per wave
 constexpr int kCommitThreads = kQuantWaves * kWave;
 constexpr int kCommitWaves = 4;  // waves per SIMD; whole prefills of 64 prompts of 1k-4k tokens: 3 171, 4 171, 5 (spills) 188 us
+
+// Few jobs go to a whole workgroup each: a wave alone takes a page's slots in up to eight
+// steps one after the other, and with a wave or two per SIMD that chain is the call (16
+// tokens to each of 128 tables: 14.5 us with four waves per token before the page jobs, 19.6
+// with a wave per page, 15.0 so).  The line lies by the bound on the jobs, four per table and the
+// tokens' own: up to 1024 (a wave per SIMD), or 2048 of longer appends (33 tokens to 256
+// tables, 1816: 16.9 and 20.5 us; but 4 tokens to 384, 1680: 17.9 and 16.9).
+constexpr int kCommitFewJobs = 1024;
+constexpr int kCommitFewTokens = 8;
 
 struct TablePlan {
     int need[2], jobs[2];
@@ -426,7 +439,7 @@ __device__ __forceinline__ void describe_job(JobDesc& d, int t, const TState& s,
     d.sold = 0;
 }
 
-// The image of one page, as the job's wave composes it in LDS.
+// The image of one page, as the job composes it in LDS.
 constexpr int kPageMax = 4736;  // largest page of the layouts
 constexpr bool page_max_covers(int li) { return li >= kNumLayouts || (layout_page_bytes(li) <= kPageMax && page_max_covers(li + 1)); }
 static_assert(page_max_covers(0), "page image");
@@ -438,13 +451,14 @@ struct PageImage {
 // still one 16-byte load (the device takes unaligned ones), but never assumed aligned.
 typedef uint32_t Fp16x8 __attribute__((ext_vector_type(4), aligned(2)));
 
-// One page job, by one wave: resolve the page ID (a new page from the table's
-// ring region), quantize the job's tokens, write them, zero a fresh page's
+// One page job, by JW waves (one, or a whole workgroup, which meets in sync()):
+// resolve the page ID (a new page from the table's ring region), quantize the job's tokens, write them, zero a fresh page's
 // unused bytes.  Lane = (row of 16, eight dims): row r takes the TT/4 page
 // slots from r * TT/4 on, one per step, so a token's key or value vector is one
 // 16-byte load per lane, a quad holds a 32-dim group, and a lane ends with its
 // dims' codes of TT/4 neighbouring slots, one piece of each dimension-major
-// value row.  The page is composed in LDS and written in 16-byte pieces: a fresh
+// value row (of JW waves each takes its part of the steps, and the pieces are or-ed
+// together).  The page is composed in LDS and written in 16-byte pieces: a fresh
 // page whole, a continued one by its new slots (its value rows or-ed with the
 // old).
 // Bound by HBM on bulk appends (fp16 rows in, pages out): 132 us for 64 prompts
@@ -452,17 +466,24 @@ typedef uint32_t Fp16x8 __attribute__((ext_vector_type(4), aligned(2)));
 // where a large copy reaches 5.1).  One wave per token with two values per
 // lane, its codes stored where they fell, took 576 us: about 250 instructions
 // per token, most of them for the sixteenfold group extremes and scale.
-template <int KB, int VB, int TT>
+template <int KB, int VB, int TT, int JW>
 __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDesc& job, PageImage& img_)
 {
     constexpr int kLbK = (1 << KB) - 1, kLbV = (1 << VB) - 1;
     constexpr int NS = TT / 4;                  // slots per row of lanes
-    constexpr int kStep = 2;                    // slots per row loaded at once (four: 128 VGPRs and spills)
-    constexpr int kAcc = NS * VB > 24 ? 2 : 1;  // value codes of NS slots: exact in one or two floats
-    constexpr int kPer = NS / kAcc;
+    constexpr int NW = NS / JW;                 // and per wave of the job
+    constexpr int kStep = JW > 1 ? NW : 2;      // slots per row loaded at once (four: 128 VGPRs and spills)
+    constexpr int kAcc = NW * VB > 24 ? 2 : 1;  // value codes of NW slots: exact in one or two floats
+    constexpr int kPer = NW / kAcc;
+    constexpr int kThr = JW * kWave;
     constexpr int kVBytes = kD * TT * VB / 8;
     const int lane = threadIdx.x & (kWave - 1);
     const int row = lane >> 4, l16 = lane & 15;
+    const int jw = JW > 1 ? wave_index() : 0, tid = jw * kWave + lane;  // wave and thread of the job
+    auto sync = [] {
+        if constexpr (JW > 1) __syncthreads();
+        else wave_lds_sync();
+    };
     const int P = a.p_max, H = a.Hkv, sec = job.sec;
     const int t = job.t, b = t / H, h = t - b * H;
     uint8_t* img = reinterpret_cast<uint8_t*>(&img_);
@@ -498,9 +519,9 @@ __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDes
             }
         }
     };
-    load_steps(0);
+    load_steps(jw * NW);
     id = __builtin_amdgcn_readfirstlane(id);
-    if (lane == 0 && job.ring_idx >= 0) trow[job.tslot] = id;
+    if (tid == 0 && job.ring_idx >= 0) trow[job.tslot] = id;
     const int off_kc = a.off_kcode[sec], off_km = a.off_kmeta[sec];
     const int off_vc = a.off_vcode[sec], off_vm = a.off_vmeta[sec];
     const int off_sc = a.off_score[sec], off_pos = a.off_pos[sec];
@@ -508,23 +529,28 @@ __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDes
     const bool page_ok = (unsigned)id < (unsigned)a.num_pages;  // never write outside the pool
     uint8_t* pg = a.pool + (long long)(page_ok ? id : 0) * a.page_bytes;
     // a page being continued keeps its earlier tokens' value code bits
-    uint4 vold[(kVBytes + 1023) / 1024];
+    constexpr int kVold = (kVBytes + 16 * kThr - 1) / (16 * kThr);
+    uint4 vold[kVold];
 #pragma unroll
-    for (int i = 0; i < (kVBytes + 1023) / 1024; ++i)
-        vold[i] = !fresh && 1024 * i + 16 * lane < kVBytes ? *reinterpret_cast<const uint4*>(pg + off_vc + 1024 * i + 16 * lane)
-                                                           : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < kVold; ++i) {
+        const int o = 16 * (i * kThr + tid);
+        vold[i] = !fresh && o < kVBytes ? *reinterpret_cast<const uint4*>(pg + off_vc + o) : make_uint4(0, 0, 0, 0);
+    }
     if (fresh)  // zero what no token covers: of a full page, the bytes past its segments
-        for (int o = (s1 < TT ? 0 : off_pos / 16 + TT / 4) + lane; o < (int)a.page_bytes / 16; o += kWave)
+        for (int o = (s1 < TT ? 0 : off_pos / 16 + TT / 4) + tid; o < (int)a.page_bytes / 16; o += kThr)
             img_.b[o] = make_uint4(0, 0, 0, 0);
-    wave_lds_sync();
+    if constexpr (JW > 1)  // the waves' value codes are or-ed together
+        if (!fresh || s1 == TT)
+            for (int o = tid; o < kVBytes / 16; o += kThr) img_.b[off_vc / 16 + o] = make_uint4(0, 0, 0, 0);
+    sync();
     float vrow[kAcc][8];
 #pragma unroll
     for (int q = 0; q < kAcc; ++q)
 #pragma unroll
         for (int d = 0; d < 8; ++d) vrow[q][d] = 0.0f;
 #pragma unroll 1
-    for (int i0 = 0; i0 < NS; i0 += kStep) {
-        if (i0 > 0) load_steps(i0);
+    for (int i0 = jw * NW; i0 < (jw + 1) * NW; i0 += kStep) {
+        if (i0 > jw * NW) load_steps(i0);
 #pragma unroll
         for (int i = 0; i < kStep; ++i) {
             if (!step_on(i0 + i)) continue;
@@ -550,7 +576,7 @@ __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDes
             const float place = on ? (float)(1 << VB * ((i0 + i) % kPer)) : 0.0f;
 #pragma unroll
             for (int q = 0; q < kAcc; ++q) {
-                const float at = (i0 + i) / kPer == q ? place : 0.0f;
+                const float at = (i0 + i - jw * NW) / kPer == q ? place : 0.0f;
 #pragma unroll
                 for (int d = 0; d < 8; ++d) vrow[q][d] = __builtin_fmaf(c[d], at, vrow[q][d]);
             }
@@ -560,61 +586,66 @@ __device__ __forceinline__ void commit_job_fmt(const AppendArgs& a, const JobDes
             }
         }
     }
-    // value rows: the piece of slots NS*row .. of dims 8*l16 ..
+    // value rows: the piece of slots NS*row + NW*jw .. of dims 8*l16 ..
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
-        uint8_t* at = img + off_vc + (8 * l16 + d) * (TT * VB / 8) + row * (NS * VB / 8);
-        if constexpr (NS * VB == 32) {
-            *reinterpret_cast<uint32_t*>(at) = (uint32_t)vrow[0][d] | (uint32_t)vrow[kAcc - 1][d] << 16;
+        uint8_t* at = img + off_vc + (8 * l16 + d) * (TT * VB / 8);
+        if constexpr (JW > 1) {
+            const int bit = (row * NS + jw * NW) * VB;
+            static_assert(kAcc == 1 && 32 % (NW * VB) == 0, "a wave's codes lie in one word");
+            atomicOr(reinterpret_cast<uint32_t*>(at + (bit >> 5) * 4), (uint32_t)vrow[0][d] << (bit & 31));
+        } else if constexpr (NS * VB == 32) {
+            *reinterpret_cast<uint32_t*>(at + row * 4) = (uint32_t)vrow[0][d] | (uint32_t)vrow[kAcc - 1][d] << 16;
         } else if constexpr (NS * VB == 16) {
-            *reinterpret_cast<uint16_t*>(at) = (uint16_t)(uint32_t)vrow[0][d];
+            *reinterpret_cast<uint16_t*>(at + row * 2) = (uint16_t)(uint32_t)vrow[0][d];
         } else {
             static_assert(NS * VB == 8, "value row pieces");
-            *at = (uint8_t)(uint32_t)vrow[0][d];
+            at[row] = (uint8_t)(uint32_t)vrow[0][d];
         }
     }
-    if (mine) {
+    if (mine && jw == 0) {
         *reinterpret_cast<float*>(img + off_sc + 4 * lane) = score;
         *reinterpret_cast<int32_t*>(img + off_pos + 4 * lane) = sold + j;
     }
-    wave_lds_sync();
+    sync();
     if (page_ok && fresh) {
-        for (int o = lane; o < (int)a.page_bytes / 16; o += kWave) reinterpret_cast<uint4*>(pg)[o] = img_.b[o];
+        for (int o = tid; o < (int)a.page_bytes / 16; o += kThr) reinterpret_cast<uint4*>(pg)[o] = img_.b[o];
     } else if (page_ok) {
         const int ns = s1 - s0;
-        for (int i = lane; i < (KB + 1) * ns; i += kWave) {  // key chunks, then key metadata
+        for (int i = tid; i < (KB + 1) * ns; i += kThr) {  // key chunks, then key metadata
             const int c = i / ns, sl = s0 + (i - c * ns);
             const int o = c < KB ? off_kc + (c * TT + sl) * 16 : off_km + sl * 16;
             *reinterpret_cast<uint4*>(pg + o) = *reinterpret_cast<const uint4*>(img + o);
         }
-        for (int i = lane; i < (kNG + 2) * ns; i += kWave) {  // value metadata, score, position
+        for (int i = tid; i < (kNG + 2) * ns; i += kThr) {  // value metadata, score, position
             const int g = i / ns, sl = s0 + (i - g * ns);
             const int o = g < kNG ? off_vm + (g * TT + sl) * 4 : (g == kNG ? off_sc : off_pos) + sl * 4;
             *reinterpret_cast<uint32_t*>(pg + o) = *reinterpret_cast<const uint32_t*>(img + o);
         }
 #pragma unroll
-        for (int i = 0; i < (kVBytes + 1023) / 1024; ++i) {
-            const int o = off_vc + 1024 * i + 16 * lane;
-            if (1024 * i + 16 * lane >= kVBytes) break;
+        for (int i = 0; i < kVold; ++i) {
+            const int o = off_vc + 16 * (i * kThr + tid);
+            if (16 * (i * kThr + tid) >= kVBytes) break;
             const uint4 v = *reinterpret_cast<const uint4*>(img + o);
             *reinterpret_cast<uint4*>(pg + o) = make_uint4(v.x | vold[i].x, v.y | vold[i].y, v.z | vold[i].z, v.w | vold[i].w);
         }
     }
-    wave_lds_sync();  // the image is reused by the wave's next job
+    sync();  // the image is reused by the next job
 }
 
 // One page job in the page format of its section (the layouts' formats; see
 // kLayoutFmts), so that row widths and bit positions are constants.
+template <int JW>
 __device__ __forceinline__ void commit_job(const AppendArgs& a, const JobDesc& job, PageImage& img)
 {
     const int sec = job.sec;
     const int kb = a.kb[sec], vb = a.vb[sec], T = a.T[sec];
-    if (kb == 8 && vb == 4) commit_job_fmt<8, 4, 16>(a, job, img);
-    else if (kb == 4 && vb == 2 && T == 32) commit_job_fmt<4, 2, 32>(a, job, img);
-    else if (kb == 8 && vb == 8) commit_job_fmt<8, 8, 16>(a, job, img);
-    else if (kb == 8 && vb == 2) commit_job_fmt<8, 2, 16>(a, job, img);
-    else if (kb == 4 && vb == 1) commit_job_fmt<4, 1, 32>(a, job, img);
-    else commit_job_fmt<4, 2, 16>(a, job, img);
+    if (kb == 8 && vb == 4) commit_job_fmt<8, 4, 16, JW>(a, job, img);
+    else if (kb == 4 && vb == 2 && T == 32) commit_job_fmt<4, 2, 32, JW>(a, job, img);
+    else if (kb == 8 && vb == 8) commit_job_fmt<8, 8, 16, JW>(a, job, img);
+    else if (kb == 8 && vb == 2) commit_job_fmt<8, 2, 16, JW>(a, job, img);
+    else if (kb == 4 && vb == 1) commit_job_fmt<4, 1, 32, JW>(a, job, img);
+    else commit_job_fmt<4, 2, 16, JW>(a, job, img);
 }
 
 // A table's state before the call, t uniform: through scalar loads (the
@@ -637,6 +668,9 @@ __device__ __forceinline__ TState uniform_state(const TState* ts, int t)
 
 constexpr int kPlanKeep = 2;  // tables per thread whose state stays in registers
 
+// JW: waves of a job, one, or all four of the workgroup where there are few jobs
+// (kCommitFewJobs).
+template <int JW>
 __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(AppendArgs a)
 {
     const int tid = threadIdx.x;
@@ -645,7 +679,8 @@ __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(Ap
     __shared__ long long s_scan[kCommitThreads / kWave];
     __shared__ uint32_t s_bits[kCommitThreads / kWave];
     __shared__ long long s_pre[kAppendPlanTables];  // exclusive prefix of every table's plan word
-    __shared__ PageImage s_img[kQuantWaves];
+    constexpr int kSide = kQuantWaves / JW;  // jobs side by side
+    __shared__ PageImage s_img[kSide];
     const long long head_old = a.flags->head_old, tail_old = a.flags->tail_old;
 
     // ---- the plan, in every workgroup (each thread a contiguous run of tables)
@@ -698,7 +733,7 @@ __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(Ap
         if (tid == 0) a.ring_ptr[0] = head_old + total_need;
     }
 
-    // ---- page jobs, one per wave at a time --------------------------------------
+    // ---- page jobs, one per wave (or workgroup) at a time -------------------------
     {
         long long pre = before;
         for_tables([&](int t, const TState& s) {
@@ -709,7 +744,8 @@ __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(Ap
     __syncthreads();
     const int lane = lane_id();
     const int stride = (NT + kWave - 1) / kWave;
-    for (int job = (int)blockIdx.x * kQuantWaves + wave_index(); job < njobs; job += (int)gridDim.x * kQuantWaves) {
+    const int side = wave_index() / JW;
+    for (int job = (int)blockIdx.x * kSide + side; job < njobs; job += (int)gridDim.x * kSide) {
         // the job's table is the last whose first job is <= job (tables without
         // jobs share their successor's prefix): among every stride-th table,
         // then among the stride tables from that one on
@@ -721,7 +757,7 @@ __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit(Ap
         const TState s = uniform_state(a.tstate, t);
         JobDesc d;
         describe_job(d, t, s, table_plan(s, P, a.tsh), read_lane<long long>(s_pre[t], 0), job, P, head_old, a.tsh);
-        commit_job(a, d, s_img[wave_index()]);
+        commit_job<JW>(a, d, s_img[side]);
     }
 }
 
@@ -841,7 +877,7 @@ __global__ __launch_bounds__(kCommitThreads, kCommitWaves) void append_commit_pl
         const TState s = uniform_state(a.tstate, t);
         JobDesc d;
         describe_job(d, t, s, table_plan(s, a.p_max, a.tsh), read_lane<long long>(a.tplan[t], 0), job, a.p_max, head_old, a.tsh);
-        commit_job(a, d, s_img[wave_index()]);
+        commit_job<1>(a, d, s_img[wave_index()]);
     }
 }
 
@@ -1010,7 +1046,7 @@ __global__ __launch_bounds__(kCommitThreads) void append_one(AppendArgs a)
         d.one = 1;
         d.off_b = __builtin_amdgcn_readfirstlane(s_job.off_b);
         d.sold = __builtin_amdgcn_readfirstlane(s_job.sold);
-        commit_job(a, d, s_img);
+        commit_job<1>(a, d, s_img);
     }
 
     // ---- the workgroup arriving last writes the state after the call
@@ -1374,14 +1410,17 @@ hipError_t launch_append(const AppendArgs& args, int grid_quant, hipStream_t st)
     const int room = kClsBusyGroups / tables;
     a.cls_split = tiles < room ? tiles : room;
     if (a.cls_split < 1) a.cls_split = 1;
-    hipError_t e = launch1(append_classify, (unsigned)(tables * a.cls_split), kClsThreads, st, a);
+    hipError_t e = launch1(a.max_new <= kClsThreads ? append_classify<1> : append_classify<kClsPer>,
+                           (unsigned)(tables * a.cls_split), kClsThreads, st, a);
     if (e != hipSuccess) return e;
     if (append_planned(a.B, a.Hkv)) {
         e = launch1(append_plan, 1, kPlanThreads, st, a);
         if (e != hipSuccess) return e;
         return launch1(append_commit_planned, (unsigned)grid_quant, kCommitThreads, st, a);
     }
-    return launch1(append_commit, (unsigned)grid_quant, kCommitThreads, st, a);
+    if (a.job_cap <= (a.max_new < kCommitFewTokens ? 1 : 2) * kCommitFewJobs)
+        return launch1(append_commit<kQuantWaves>, (unsigned)max(a.job_cap, 1), kCommitThreads, st, a);
+    return launch1(append_commit<1>, (unsigned)grid_quant, kCommitThreads, st, a);
 }
 
 hipError_t launch_alloc(const AllocArgs& a, hipStream_t st)

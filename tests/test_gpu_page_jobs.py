@@ -1,4 +1,4 @@
-"""Page jobs of the append, one wave per page: fresh and continued pages with the job's
+"""Page jobs of the append, one wave or one workgroup per page: fresh and continued pages with the job's
 slots starting and ending anywhere (each lane row's first and last slot, one slot, a whole
 page), every page format, and groups at the quantizer's edges.  Bit-exact against the oracle."""
 import numpy as np
@@ -33,7 +33,8 @@ def edge_values(rng, rows, Hkv):
 
 
 @pytest.mark.parametrize("layout", range(4))
-@pytest.mark.parametrize("B,Hkv", [(5, 3), (70, 15)])  # the plan in every workgroup, and planned once
+# few jobs, a workgroup each; a wave each, the plan in every workgroup; and planned once
+@pytest.mark.parametrize("B,Hkv", [(5, 3), (70, 8), (70, 15)])
 def test_page_jobs_bitexact(layout, B, Hkv):
     rng = np.random.default_rng(300 + layout)
     Lo, Ld = layouts(max_seq_len=192, **LAYOUTS[layout])
