@@ -1421,7 +1421,7 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
 //   sum of p / (W - T) for tables that are few beside W (kOwnFew): the ranges are then
 //                      about as long as the cut list's W + T pieces.
 // Longer ranges would be faster (one sequence of 8000 and 32768 tokens at GQ 4: 13.3
-// and 18.8 us with 2 sqrt(p) units, 15.7 and 24.7 now, 117 and 111 cut; 16 sequences of 2000
+// and 18.8 us with 2 sqrt(p) units, 16.1 and 24.4 now, 129 and 125 cut; 16 sequences of 2000
 // tokens, 128 tables: 16.1 with 98 units, 19.5 cut; 5 of 1000 to 6000 at GQ 7, 20 tables:
 // 16.5 with 43, 23.6 cut), but a wave's weights are fp16 relative to the largest of its
 // chain, so the error against 64 bits grows with the chain.  With ranges as long as it

@@ -188,7 +188,7 @@ __device__ __forceinline__ TInt block_excl_scan(TInt x, TInt* lds, TInt* total, 
     return below + inc - x;
 }
 
-// The same for a true 64-bit value per thread (0 <= x, sum below 2^52), as two
+// The same for a true 64-bit value per thread (0 <= x, sum below 2^51), as two
 // 32-bit counters, its low 20 bits and the rest: those are added through DPP,
 // where a 64-bit sum would pass every step through LDS.
 __device__ __forceinline__ long long block_excl_scan_wide(long long x, long long* lds, long long* total, uint32_t bits = 0,
