@@ -227,8 +227,8 @@ diffkv_status diffkv_quantize_append(const diffkv_layout* layout, const diffkv_c
  *        list of work units (a high page 3, a 32-token low page 6, a 16-token
  *        low page 3, a table's start 50) cut into one equal
  *        share per resident workgroup -- or, where that is little work per
- *        workgroup, every table is cut into equal ranges of its own, of at most
- *        one high page per wave; a table spread over several shares has
+ *        workgroup, every table is cut into equal ranges of its own, as short as
+ *        the workgroups allow; a table spread over several shares has
  *        their (max, sum, acc) states merged in page order (Sec. 6.2 sequence
  *        split).  S >= 1: each table is cut into min(S, pages) equal page
  *        ranges, merged the same way (S = 1: no split, no merge).  Results

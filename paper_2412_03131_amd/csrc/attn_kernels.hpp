@@ -1413,23 +1413,27 @@ __device__ __forceinline__ int longest_first(const AttnArgs& a, AttnShared<GQ, N
 // arrivals and merge were the whole call (190 us; 9.5 now).  Shares that cross a
 // table boundary also cost a second segment start and a second arrival.  So every
 // table is cut into ceil(p / quantum) equal ranges of its p page units, one workgroup
-// each, a table in one range having no merge, wherever these ranges fit the W resident
-// workgroups with a quantum of
-//   kOwnUnits          a high page for every wave: the longest chain of v_dot2 sums in a
-//                      wave is then one page, the shortest there is, whatever the cut
-//                      list's would be;
-//   sum of p / (W - T) for tables that are few beside W (kOwnFew): the ranges are then
-//                      about as long as the cut list's W + T pieces.
-// Longer ranges would be faster (one sequence of 8000 and 32768 tokens at GQ 4: 13.3
-// and 18.8 us with 2 sqrt(p) units, 16.1 and 24.4 now, 129 and 125 cut; 16 sequences of 2000
-// tokens, 128 tables: 16.1 with 98 units, 19.5 cut; 5 of 1000 to 6000 at GQ 7, 20 tables:
-// 16.5 with 43, 23.6 cut), but a wave's weights are fp16 relative to the largest of its
-// chain, so the error against 64 bits grows with the chain.  With ranges as long as it
-// takes to fit W workgroups it is 0.99 times the cut list's for T up to W / 32 (60
-// calls, geometric mean), 1.04 from there to W / 16 and up to 1.39 above.
+// each, a table in one range having no merge, with the least quantum whose ranges fit
+// the W resident workgroups:
+//   kOwnUnits              a high page for every wave: the longest chain of v_dot2 sums
+//                          in a wave is then one page, the shortest there is;
+//   P / (W - held / 2)     P the page units of the `held` tables that have pages: their
+//                          last ranges waste half a range each on average;
+//   P / (W - held)         fits always.
+// (Each is tried by counting its ranges, 0.3 us; where the first cannot fit the second
+// comes at once, for all T tables.)
+// A wave's weights are fp16 relative to the largest of its chain, so the error against
+// 64 bits grows with the chain, and the quantum counts page units alone: with the
+// tables' starts in it (total / (W - T)) the error was 1.01 times the cut list's for T
+// from W / 32 to W / 16, 1.04 to W / 8, 1.06 to W / 4 and 1.20 to W / 2; so it is 1.00, 1.00,
+// 0.97 and 0.93 (36 calls each, geometric means).  Longer ranges would be faster for
+// one sequence (8000 and 32768 tokens at GQ 4: 13.3 and 18.8 us with 2 sqrt(p) units, 16.4
+// and 25.1 now, 116 and 123 cut).
+// Rounding up to whole ranges makes the longest share total / (W - T) at most where the
+// cut list has total / W plus a segment's start, so beyond kOwnUnits the line lies where
+// the two differ by Units::seg (16 sequences of 8192 tokens, over the line: 31.5 us cut).
 template <int LI, int NW>
 constexpr int kOwnUnits = NW * Units<LI>::hi;
-constexpr int kOwnFew = 32;
 
 // Ranges of a table of `units` units (0: empty).
 template <int LI>
@@ -1510,15 +1514,17 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
     }
     long long total;
     const long long before = block_excl_scan_wide(mine, sh.scan, &total);
+    if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
     if (threadIdx.x == 0) {
         sh.units = total;  // read back by the arrival (not kept in registers)
         sh.own_n = 0;
     }
     long long b_lo, b_hi;
-    // (the ranges hold all page units, so more than W * kOwnUnits of these never fit)
     int own = 0, at = 0, quantum = kOwnUnits<LI, NW>;
-    const bool few = T * kOwnFew <= W && total * T <= Units<LI>::seg * W * (W - T);
-    if (few || (T <= W && total <= W * quantum + (long long)T * Units<LI>::seg)) {
+    const bool little = T < W && total * T <= Units<LI>::seg * W * (W - T);
+    const long long least = total - (long long)T * Units<LI>::seg;  // page units, if no table is empty
+    const bool fit = least <= W * quantum;                          // (else such ranges never do)
+    if (little || (T <= W && fit)) {
         int held = 0;  // tables with pages
         auto count = [&]() {
             long long cnt = 0, all;  // ranges, and tables with pages in the upper half
@@ -1530,14 +1536,21 @@ __global__ __launch_bounds__(attn_waves(GQ, LI) * kWave, attn_blocks_per_cu(GQ, 
             own = (int)all;
             held = (int)(all >> 32);
         };
+        auto part = [](long long p, int n) { return (int)((p + n - 1) / n); };
+        if (!fit) quantum = part(least, (int)W - T / 2);
         count();
-        if (few && own > W) {
-            const int pages = (int)(total - (long long)held * Units<LI>::seg), room = (int)W - held;
-            quantum = (pages + room - 1) / room;
-            count();
+        if (little && own > W) {
+            const long long pages = total - (long long)held * Units<LI>::seg;
+            if (fit) {
+                quantum = part(pages, (int)W - held / 2);
+                count();
+            }
+            if (own > W) {
+                quantum = part(pages, (int)W - held);
+                count();
+            }
         }
     }
-    if (claim) arrive_claim_once(a.arrive + k, word, call_tag());
     if (own <= W && own > 0) {
         if (k >= own) return;
         long long u = before;

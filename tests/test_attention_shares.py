@@ -30,14 +30,19 @@ def page_at_unit(x, ph, np_):
 def quantum_of(tabs, T, W, waves):
     """The range length of tables [(ph, pl)], or None where the list is cut."""
     pus = [HI * a + LO * b for a, b in tabs if a + b]
-    total = sum(pus) + SEG * len(pus)
-    few = 32 * T <= W and total * T <= SEG * W * (W - T)
-    q = waves * HI
-    if not few and (T > W or total > W * q + T * SEG):
+    total, held = sum(pus) + SEG * len(pus), len(pus)
+    little = T < W and total * T <= SEG * W * (W - T)
+    fit = total - SEG * T <= W * waves * HI
+    if not little and (T > W or not fit):
         return None
-    if few and sum(-(-p // q) for p in pus) > W:
-        q = -(-sum(pus) // (W - len(pus)))
-    return q if 0 < sum(-(-p // q) for p in pus) <= W else None
+    part = lambda p, n: -(-p // n)
+    tries = [waves * HI if fit else part(total - SEG * T, W - T // 2)]
+    if little:
+        tries += [part(sum(pus), W - held // 2)] * fit + [part(sum(pus), W - held)]
+    for q in tries:
+        if sum(-(-p // q) for p in pus) <= W:
+            return q if pus else None
+    return None
 
 
 def ranges_of(ph, pl, quantum):
@@ -48,9 +53,9 @@ def ranges_of(ph, pl, quantum):
 
 
 def test_own_shares_cover_every_page_once():
-    """Every page lies in one range, and no range holds more than one page per wave (the length of a
-    wave's chain, on which the error depends), or, with few tables, is longer than the shares of
-    the cut list by more than their number falls behind its W + T pieces."""
+    """Every page lies in one range, the ranges fit the workgroups, and no range holds more than one
+    page per wave (the length of a wave's chain, on which the error depends) where such ranges
+    fit, nor more page units than a workgroup's part where every table wastes a range."""
     rng = random.Random(5)
     checked = longer = 0
     for _ in range(6000):
@@ -62,10 +67,13 @@ def test_own_shares_cover_every_page_once():
         if q is None:
             continue
         checked += 1
+        assert sum(-(-(HI * a + LO * b) // q) for a, b in tabs) <= W
         total = sum(SEG + HI * a + LO * b for a, b in tabs if a + b)
         if q > waves * HI:
             longer += 1
-            assert 32 * T <= W and q <= total / W * (W / (W - T)) + 1
+            held = sum(a + b > 0 for a, b in tabs)
+            assert sum(-(-(HI * a + LO * b) // (waves * HI)) for a, b in tabs) > W
+            assert q <= (total - SEG * held) / (W - held) + 1
         for a, b in tabs:
             if a + b == 0:
                 continue
@@ -114,8 +122,9 @@ def test_one_attempt_claim_loses_no_arrival():
     (3, 1, 8, 0, (2600, 300, 0)),               # twelve waves, an empty table
     (5, 1, 7, 1, (33, 500, 1100, 1700, 2300)),  # one to eight ranges, 8-bit values
     (4, 2, 3, 2, (1900, 900, 450, 60)),
-    (2, 4, 8, 0, (9000, 7000)),                 # few tables, ranges longer than a page per wave
-    (2, 4, 6, 3, (6000, 0)),                    # the same with empty tables
+    (2, 4, 8, 0, (9000, 7000)),                 # ranges longer than a page per wave
+    (16, 8, 4, 0, (2000, 1800, 1500, 40)),      # the same with tables of one to four ranges
+    (2, 4, 6, 3, (6000, 0)),                    # with empty tables
 ])
 def test_own_shares_match_oracle(B, Hkv, gq, layout, lens):
     import torch
