@@ -35,10 +35,10 @@
 //
 // Bound by the matrix cores and, in the row pass, VALU issue about equally (one
 // exp2 is two slots): 64 prompts of 1k-4k tokens at 32 / 8 heads, 2 x 1.73
-// TFLOP, take 2.0 + 1.95 ms, 870 TFLOP/s, where a large library fp16 product
+// TFLOP, take 1.95 + 1.98 ms, 880 TFLOP/s, where a large library fp16 product
 // reaches 1260 on the device.  With 16x16 tiles through AGPRs, register-staged
 // and one workgroup per block it was 2.7 + 2.8 ms; of that, the 32x32 tiles
-// gave 0.4 and 0.1, work queues instead of workgroups per block (below) 0.3
+// gave 0.4 and 0.1, work lists instead of workgroups per block (below) 0.3
 // and 0.6.
 
 #include "internal.hpp"
